@@ -19,15 +19,20 @@
 // group's 8 channels are summed per row and stored; sigma_reduce_kernel adds
 // the 8 groups in order and takes the square root.
 //
+// sigma_lowpass_kernel: the same for the small kappa that the tier uses, the
+// transform in registers and only its kept bins formed.
+//
 // sigma_select_kernel: one workgroup per sequence.  The tier is the first
 // nsink rows plus the top-m of the other closed rows by (sigma desc, row asc):
-// an MSB-first radix select over the fp64 bit patterns (sigma >= 0, so the
-// bits order like the values) finds the m-th key, then one ordered pass
-// writes the rows above it and the first rows equal to it, ascending.
+// the m-th key over the fp64 bit patterns (sigma >= 0, so the bits order like
+// the values), then one ordered pass writes the rows above it and the first
+// rows equal to it, ascending.
 //
 // Also here: the flags of a caller's tier (for the step on a given kept set)
 // and the all-layer CSR pack of row lists (offsets by one block's prefix sum,
 // then one copy per list).
+#include <type_traits>
+
 #include "vkv_internal.h"
 
 namespace vkv {
@@ -170,6 +175,226 @@ __global__ __launch_bounds__(SG_THREADS) void sigma_fft_kernel(SigmaArgs a) {
     for (int m = 0; m < SG_ROWS; ++m) out[tid + SG_THREADS * m] = acc[m];
 }
 
+// The same for kappa <= SG_KLOW, the kept bins of the tier's own settings (16
+// and 64): the transform in three radix-16 passes held in registers, of which
+// only the kept bins' part is formed.  With t = 256 t2 + 16 t1 + t0 and
+// f = f0 + 16 f1 + 256 f2, w = exp(-2 pi i / 4096):
+//   A[f0; t1 t0] = w^((16 t1 + t0) f0) sum_t2 x[t] w16^(t2 f0)   thread (t1, t0)
+//   B[f0 f1; t0] = sum_t1 A[f0; t1 t0] w16^(t1 f1)               thread (f0, t0)
+//   X[f]         = sum_t0 B[f0 f1; t0] w256^(t0 (f1 + 16 f2))    over 16 lanes
+// The bins f < 64 have f2 = 0, f1 < 4, the bins f > N - 64 have f2 = 15,
+// f1 >= 12: eight values of f1, each with one f2, so a thread forms 8 of its 16
+// B's, the last pass is a 16-lane sum per B, and the inverse runs back the same
+// way from the same registers.  A and its inverse are the only exchanges
+// through LDS, each written to and read from the thread's own places on one
+// side, so two barriers serve a pair of channels (24 LDS passes and barriers in
+// the stage-by-stage form above).  The rows' 8 bytes of two pairs are read at
+// once.  The 8 channel groups of a block share its cache lines, so they go to
+// one XCD (consecutive workgroup ids go round the 8 XCDs).
+// Bound by fp64 issue (about 1400 vector instructions per thread and pair) and
+// the strided 8-byte row reads.  Measured at 8 x 32 blocks of rows: 836 -> 165 us.
+constexpr int SG_KLOW = 64;
+constexpr int64_t SG_KLOW_STRIDE = 1 << 22;   // row stride (elements) whose lane offsets fit 32 bits
+constexpr size_t SG_KLOW_LDS = SG_LDS + 128 * sizeof(double2);
+
+template <bool INV>
+__device__ __forceinline__ double2 mul_i(double2 a) {   // a * -i (forward w4) or a * i
+    return INV ? make_double2(-a.y, a.x) : make_double2(a.y, -a.x);
+}
+
+// four-point transform in place: (a, b, c, d) -> outputs 0..3
+template <bool INV>
+__device__ __forceinline__ void dft4(double2& a, double2& b, double2& c, double2& d) {
+    const double2 apc = cadd(a, c), amc = csub(a, c), bpd = cadd(b, d), bmd = mul_i<INV>(csub(b, d));
+    a = cadd(apc, bpd);
+    b = cadd(amc, bmd);
+    c = csub(apc, bpd);
+    d = csub(amc, bmd);
+}
+
+// a * w16^k (forward) or a * w16^-k, k = 0..9 with k = b c, b, c < 4
+template <bool INV, int K>
+__device__ __forceinline__ double2 mul_w16(double2 a) {
+    constexpr double C1 = 0.92387953251128675613, S1 = 0.38268343236508977173, R = 0.70710678118654752440;
+    if constexpr (K == 0) return a;
+    if constexpr (K == 4) return mul_i<INV>(a);
+    if constexpr (K == 2) return INV ? make_double2(R * (a.x - a.y), R * (a.x + a.y)) : make_double2(R * (a.x + a.y), R * (a.y - a.x));
+    if constexpr (K == 6) return mul_i<INV>(mul_w16<INV, 2>(a));
+    if constexpr (K == 1 || K == 3 || K == 9) {
+        constexpr double c = K == 1 ? C1 : (K == 3 ? S1 : -C1), s = K == 1 ? S1 : (K == 3 ? C1 : -S1);
+        return INV ? cmulc(a, make_double2(c, -s)) : cmul(a, make_double2(c, -s));
+    }
+    return a;
+}
+
+// x[4 a + b] -> first layer over a, the twiddles w16^(b c): x[4 c + b]
+template <bool INV>
+__device__ __forceinline__ void dft16_columns(double2 (&x)[16]) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) dft4<INV>(x[b], x[4 + b], x[8 + b], x[12 + b]);
+}
+template <bool INV>
+__device__ __forceinline__ void dft16_twiddles(double2 (&x)[16]) {
+    x[5] = mul_w16<INV, 1>(x[5]);
+    x[6] = mul_w16<INV, 2>(x[6]);
+    x[7] = mul_w16<INV, 3>(x[7]);
+    x[9] = mul_w16<INV, 2>(x[9]);
+    x[10] = mul_w16<INV, 4>(x[10]);
+    x[11] = mul_w16<INV, 6>(x[11]);
+    x[13] = mul_w16<INV, 3>(x[13]);
+    x[14] = mul_w16<INV, 6>(x[14]);
+    x[15] = mul_w16<INV, 9>(x[15]);
+}
+
+// sum over the 16 lanes of each row of the wave, in all of them
+__device__ __forceinline__ double rowsum16_f64(double v) {
+    auto perm = [](double x, auto ctrl) __attribute__((always_inline)) {
+        const uint64_t u = d2u(x);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, decltype(ctrl)::value, 0xF, 0xF, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), decltype(ctrl)::value, 0xF, 0xF, true);
+        return u2d(((uint64_t)hi << 32) | lo);
+    };
+    v += perm(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
+    v += perm(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
+    v += perm(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
+    v += perm(v, std::integral_constant<int, 0x140>{});   // row_mirror
+    return v;
+}
+
+__global__ __launch_bounds__(SG_THREADS, 2) void sigma_lowpass_kernel(SigmaArgs a) {
+    extern __shared__ __align__(16) uint8_t sg_lds[];
+    double2* X = reinterpret_cast<double2*>(sg_lds);                             // [f0][16 t1 + t0]
+    double2* ph = X + SG_N;   // [8][16] phases of the last pass: w256^(t0 (f1 + 16 f2)), f1 + 16 f2 = c, 252 + c
+    double* ct = reinterpret_cast<double*>(ph + 128);
+    // workgroup id -> (block of rows, channel group): 8 consecutive ids on one
+    // XCD (ids 8 apart) are the 8 groups of one block
+    const int64_t id = blockIdx.x, idx = id >> 3, job = (idx >> 3) * 8 + (id & 7);
+    const int grp = (int)(idx & 7);
+    if (job >= (int64_t)a.nblk * a.B) return;
+    const int blk = (int)(job % a.nblk), b = (int)(job / a.nblk), tid = threadIdx.x;
+    for (int j = tid; j <= SG_Q4; j += SG_THREADS)
+        ct[j] = (j == 0) ? 1.0 : (j == SG_Q4 ? 0.0 : cospi((double)j / (double)(SG_N / 2)));
+    // uniform base, one 32-bit lane offset: the 16 row addresses cost no registers
+    const uint8_t* base = reinterpret_cast<const uint8_t*>(a.cache + (int64_t)b * a.cbs +
+                                                           (a.t0 + (int64_t)blk * SG_N) * a.crs + D_LAT + 8 * grp);
+    const uint32_t rowb = (uint32_t)(2 * a.crs), lane_off = (uint32_t)tid * rowb;
+    const int f0 = tid >> 4, t0 = tid & 15;
+    double acc[16];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) acc[m] = 0.0;
+    __syncthreads();
+    if (tid < 128) {
+        const int c = tid >> 4;
+        ph[tid] = sg_twiddle(ct, (16 * (tid & 15) * (c < 4 ? c : 248 + c)) & (SG_N - 1));
+    }
+    // w^(tid f), f = c + 4 d, as a product of two (all 15 do not fit the registers)
+    double2 w1[4], w4[4];
+#pragma unroll
+    for (int f = 1; f < 4; ++f) {
+        w1[f] = sg_twiddle(ct, tid * f);
+        w4[f] = sg_twiddle(ct, tid * 4 * f);
+    }
+    auto tw = [&](int c, int d) __attribute__((always_inline)) {
+        return c == 0 ? w4[d] : (d == 0 ? w1[c] : cmul(w1[c], w4[d]));
+    };
+    // (an opaque copy per use: the compiler would otherwise keep the 9 products,
+    // and below the 16 row addresses, across the loop in scratch memory)
+    auto hide = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int f = 1; f < 4; ++f) asm volatile("" : "+v"(w1[f].x), "+v"(w1[f].y), "+v"(w4[f].x), "+v"(w4[f].y));
+    };
+    // one pair of channels, the rows' values in w (bf16 bits, two a word)
+    auto one_pair = [&](const uint32_t (&w)[16]) __attribute__((always_inline)) {
+        double2 x[16];
+        auto input = [&](int m) __attribute__((always_inline)) {
+            return make_double2((double)__uint_as_float(w[m] << 16), (double)__uint_as_float(w[m] & 0xFFFF0000u));
+        };
+#pragma unroll
+        for (int m = 0; m < 16; ++m) x[m] = input(m);
+        dft16_columns<false>(x);
+        dft16_twiddles<false>(x);
+        hide();
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            dft4<false>(x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {   // output f = c + 4 d
+                const int f = c + 4 * d;
+                X[SG_THREADS * f + tid] = f ? cmul(x[4 * c + d], tw(c, d)) : x[4 * c + d];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < 16; ++m) x[m] = X[SG_THREADS * f0 + 16 * m + t0];
+        dft16_columns<false>(x);
+        dft16_twiddles<false>(x);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            // outputs f1 = c (d = 0) and f1 = 12 + c (d = 3: w4^(3b) = i^b)
+            const double2 u = cadd(x[4 * c], x[4 * c + 2]), v = cadd(x[4 * c + 1], x[4 * c + 3]);
+            const double2 p = csub(x[4 * c], x[4 * c + 2]), q = csub(x[4 * c + 1], x[4 * c + 3]);
+            double2 lo = cadd(u, v), hi = make_double2(p.x - q.y, p.y + q.x);
+            // X[f] for f = f0 + 16 c and f = 4096 - 64 + 16 c + f0
+            const double2 wl = ph[16 * c + t0], wh = ph[16 * (4 + c) + t0];
+            lo = cmul(lo, wl);
+            hi = cmul(hi, wh);
+            lo = make_double2(rowsum16_f64(lo.x), rowsum16_f64(lo.y));
+            hi = make_double2(rowsum16_f64(hi.x), rowsum16_f64(hi.y));
+            const double kl = (f0 + 16 * c < a.kappa) ? 1.0 : 0.0;
+            const double kh = (SG_N - 64 + 16 * c + f0 > SG_N - a.kappa) ? 1.0 : 0.0;
+            lo = cmulc(kl != 0.0 ? lo : make_double2(0.0, 0.0), wl);
+            hi = cmulc(kh != 0.0 ? hi : make_double2(0.0, 0.0), wh);
+            // the inverse's layer over d: w4^(-3 b) = (-i)^b
+            x[4 * c] = cadd(lo, hi);
+            x[4 * c + 1] = make_double2(lo.x + hi.y, lo.y - hi.x);
+            x[4 * c + 2] = csub(lo, hi);
+            x[4 * c + 3] = make_double2(lo.x - hi.y, lo.y + hi.x);
+        }
+        dft16_twiddles<true>(x);
+        dft16_columns<true>(x);   // over c: x[4 a + b]
+#pragma unroll
+        for (int m = 0; m < 16; ++m) X[SG_THREADS * f0 + 16 * m + t0] = x[m];
+        __syncthreads();
+        hide();
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int f = c + 4 * d;
+                const double2 v = X[SG_THREADS * f + tid];
+                x[4 * c + d] = f ? cmulc(v, tw(c, d)) : v;
+            }
+            dft4<true>(x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]);
+        }
+        dft16_twiddles<true>(x);
+        dft16_columns<true>(x);
+        constexpr double inv_n = 1.0 / SG_N;
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+            const double2 v = input(m);
+            const double dx = fma(-inv_n, x[m].x, v.x), dy = fma(-inv_n, x[m].y, v.y);
+            acc[m] = fma(dx, dx, fma(dy, dy, acc[m]));
+        }
+    };
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+        uint32_t lo[16], hi[16], off = lane_off;
+        const uint8_t* rows = base + 8 * half;
+#pragma unroll
+        for (int m = 0; m < 16; ++m, rows += (uint64_t)SG_THREADS * rowb) {
+            asm volatile("" : "+s"(rows), "+v"(off));
+            const uint2 v = *reinterpret_cast<const uint2*>(rows + off);
+            lo[m] = v.x;
+            hi[m] = v.y;
+        }
+        one_pair(lo);
+        one_pair(hi);
+    }
+    double* out = a.part + (((int64_t)b * a.nblk + blk) * SG_GROUPS + grp) * SG_N;
+#pragma unroll
+    for (int m = 0; m < 16; ++m) out[tid + SG_THREADS * m] = acc[m];
+}
+
 __global__ __launch_bounds__(256) void sigma_reduce_kernel(SigmaArgs a) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;   // row within the closed range
     const int b = blockIdx.y;
@@ -186,10 +411,17 @@ size_t sigma_workspace_bytes(int64_t B, int64_t nblk) { return (size_t)(B * nblk
 
 hipError_t launch_sigma(const SigmaArgs& a, hipStream_t s) {
     if (a.nblk == 0 || a.B == 0) return hipSuccess;
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&sigma_fft_kernel),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)SG_LDS);
-    hipLaunchKernelGGL(sigma_fft_kernel, dim3(SG_GROUPS, (unsigned)a.nblk, (unsigned)a.B), dim3(SG_THREADS), SG_LDS,
-                       s, a);
+    const int64_t jobs = (a.nblk * a.B + 7) / 8 * 8 * SG_GROUPS;
+    if (a.kappa <= SG_KLOW && a.crs <= SG_KLOW_STRIDE && jobs <= INT32_MAX) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&sigma_lowpass_kernel),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)SG_KLOW_LDS);
+        hipLaunchKernelGGL(sigma_lowpass_kernel, dim3((unsigned)jobs), dim3(SG_THREADS), SG_KLOW_LDS, s, a);
+    } else {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&sigma_fft_kernel),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)SG_LDS);
+        hipLaunchKernelGGL(sigma_fft_kernel, dim3(SG_GROUPS, (unsigned)a.nblk, (unsigned)a.B), dim3(SG_THREADS),
+                           SG_LDS, s, a);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t rows = (int64_t)a.nblk * SG_N;
@@ -201,91 +433,315 @@ hipError_t launch_sigma(const SigmaArgs& a, hipStream_t s) {
 
 constexpr int SS_THREADS = 1024;
 constexpr int SS_WAVES = SS_THREADS / 64;
+constexpr int SS_PER = 8;              // keys per thread and round, all loads in flight
+constexpr int SS_LIST = 12288;         // keys near the threshold held in LDS
+constexpr int SS_SAMPLE = 2048;        // keys sampled to place the bracket around it
+constexpr int SS_BINS = 2048;          // bins of the sample's histogram
+constexpr int SS_WORDS = 2048;         // 64-row mask words of an output segment (131072 rows)
 
-// exclusive count of set flags below this lane in the block, and the block total
-__device__ __forceinline__ int block_rank(bool f, int* s_w, int tid, int* total) {
-    const uint64_t bal = __ballot(f);
-    const int lane = tid & 63, w = tid >> 6;
-    const int below = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) s_w[w] = __popcll(bal);
+// What bounds it: one workgroup reads its sequence's keys twice, so the time is
+// that of 2 x 8 n bytes through one CU plus a few barriers (there is no scratch
+// buffer through which workgroups could share a sequence).  A sample brackets
+// the take-th key; the first pass counts the keys above the bracket and lists
+// those inside it in LDS, where a radix select finds the threshold; the second
+// writes the rows above it, and the first rows equal to it, in order: 64-row
+// masks of a segment go to LDS, one scan over their counts places every word.
+// A bracket that misses or a list that overflows (ties, adversarial orders)
+// falls back to radix passes over all keys.  Measured at 8 x 131072 keys,
+// m = 4092: 473 -> 78 us (nine passes of one load per thread and round before);
+// the first pass, through a cold cache, takes about half of it.
+
+// exclusive prefix over the threads of (lo, hi) halves of a 64-bit pair, and the totals
+__device__ __forceinline__ uint64_t ss_scan(uint64_t v, uint64_t* s_w, uint64_t& total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint64_t incl = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t t = __shfl_up((unsigned long long)incl, o);
+        if (lane >= o) incl += t;
+    }
+    if (lane == 63) s_w[w] = incl;
     __syncthreads();
-    int off = 0, tot = 0;
+    uint64_t before = 0, tot = 0;
     for (int i = 0; i < SS_WAVES; ++i) {
-        const int c = s_w[i];
-        off += (i < w) ? c : 0;
+        const uint64_t c = s_w[i];
+        before += i < w ? c : 0;
         tot += c;
     }
     __syncthreads();
-    *total = tot;
-    return off + below;
+    total = tot;
+    return before + incl - v;
+}
+
+// in wave 0: the digit d of a 256-bin histogram where the count of entries in
+// digits >= d first reaches `need`, and the count above it
+__device__ __forceinline__ void ss_pick(const uint32_t* hist, int64_t need, int* s_d, int64_t* s_above) {
+    const int lane = threadIdx.x & 63;
+    uint32_t h[4], loc = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) loc += h[j] = hist[4 * lane + j];
+    uint32_t suf = loc;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_down(suf, o);
+        if (lane + o < 64) suf += t;
+    }
+    int64_t run = suf - loc;
+    if (run < need && need <= (int64_t)suf) {
+#pragma unroll
+        for (int j = 3; j >= 0; --j) {
+            if (run < need && need <= run + (int64_t)h[j]) {
+                *s_d = 4 * lane + j;
+                *s_above = run;
+            }
+            run += h[j];
+        }
+    }
+}
+
+// the need-th largest of the `cnt` keys of key[0 .. cnt) that agree with
+// `prefix` on the bits of `mask`, digit by digit from `shift` down; need becomes
+// the rank among the keys equal to the result
+template <typename Get>
+__device__ __forceinline__ uint64_t ss_radix(Get key, int64_t cnt, uint64_t prefix, uint64_t mask, int shift,
+                                             int64_t& need, uint32_t* hist, int* s_d, int64_t* s_above, uint64_t* s_key) {
+    const int tid = threadIdx.x;
+    for (;; shift -= 8) {
+        const int sh = shift < 0 ? 0 : shift;   // the last digit may overlap bits already fixed
+        if (tid < 256) hist[tid] = 0;
+        __syncthreads();
+        for (int64_t i = tid; i < cnt; i += SS_THREADS) {
+            const uint64_t k = key(i);
+            if ((k & mask) == prefix) atomicAdd(&hist[(k >> sh) & 255u], 1u);
+        }
+        __syncthreads();
+        if (tid < 64) ss_pick(hist, need, s_d, s_above);
+        __syncthreads();
+        prefix |= (uint64_t)*s_d << sh;
+        mask |= 255ull << sh;
+        need -= *s_above;
+        const bool single = hist[*s_d] == 1;
+        if (sh == 0) return prefix;
+        if (single) {   // one key left: its other digits are read off
+            for (int64_t i = tid; i < cnt; i += SS_THREADS) {
+                const uint64_t k = key(i);
+                if ((k & mask) == prefix) *s_key = k;
+            }
+            __syncthreads();
+            return *s_key;
+        }
+        __syncthreads();
+    }
 }
 
 __global__ __launch_bounds__(SS_THREADS) void sigma_select_kernel(SigmaSelArgs a) {
-    __shared__ uint32_t hist[256];
-    __shared__ int s_w[SS_WAVES];
-    __shared__ uint64_t s_prefix;
-    __shared__ int64_t s_need;
-    const int b = blockIdx.x, tid = threadIdx.x;
+    __shared__ __align__(16) uint64_t s_list[SS_LIST];   // then the segment's masks
+    __shared__ uint32_t s_h[SS_BINS];
+    __shared__ uint64_t s_w[SS_WAVES];
+    __shared__ uint64_t s_br[2];
+    __shared__ double s_mm[2][SS_WAVES];
+    __shared__ uint32_t s_cnt[2];                        // keys above the bracket, keys inside it
+    __shared__ int s_d;
+    __shared__ int64_t s_above;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t* key = reinterpret_cast<const uint64_t*>(a.sigma + (int64_t)b * a.sstride);
     int32_t* out = a.kept + (int64_t)b * a.kstride;
     const int64_t lo = a.n < a.nsink ? a.n : a.nsink;
     const int64_t navail = a.n - lo;
     const int64_t take = a.m < navail ? a.m : navail;
-    // the take-th largest key among rows [lo, n): MSB-first, 8 bits per pass
-    uint64_t prefix = 0, mask = 0;
+    const bool all = take == navail;
+    // the take-th largest key among rows [lo, n) and the rank `need` among its equals
+    uint64_t thr = 0;
     int64_t need = take;
-    if (take > 0 && take < navail) {
-        for (int pass = 0; pass < 8; ++pass) {
-            const int shift = 56 - 8 * pass;
-            if (tid < 256) hist[tid] = 0;
-            __syncthreads();
-            for (int64_t u = lo + tid; u < a.n; u += SS_THREADS) {
-                const uint64_t k = key[u];
-                if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
+    if (take > 0 && !all) {
+        const uint64_t* ka = key + lo;
+        uint64_t blo = 0, bhi = ~0ull;   // the bracket (inclusive bits)
+        if (tid < 2) s_cnt[tid] = 0;
+        if (navail > SS_LIST) {
+            // SS_SAMPLE keys at even spacing, in a linear histogram of their range
+            uint64_t sk[2];
+            double mn = INFINITY, mx = -INFINITY;
+            const int64_t stride = navail / SS_SAMPLE;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) sk[j] = ka[(int64_t)(tid + SS_THREADS * j) * stride];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                mn = fmin(mn, u2d(sk[j]));
+                mx = fmax(mx, u2d(sk[j]));
             }
+            for (int o = 32; o > 0; o >>= 1) {
+                mn = fmin(mn, __shfl_xor(mn, o));
+                mx = fmax(mx, __shfl_xor(mx, o));
+            }
+            if (lane == 0) {
+                s_mm[0][wave] = mn;
+                s_mm[1][wave] = mx;
+            }
+            for (int i = tid; i < SS_BINS; i += SS_THREADS) s_h[i] = 0;
             __syncthreads();
+            for (int w = 0; w < SS_WAVES; ++w) {
+                mn = fmin(mn, s_mm[0][w]);
+                mx = fmax(mx, s_mm[1][w]);
+            }
+            const double range = mx - mn;
+            const double sc = (range > 0.0 && range < INFINITY) ? (double)SS_BINS / range : 0.0;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const double t = (u2d(sk[j]) - mn) * sc;
+                const int bin = t > 0.0 ? (t < (double)SS_BINS ? (int)t : SS_BINS - 1) : 0;
+                atomicAdd(&s_h[bin], 1u);
+            }
             if (tid == 0) {
-                int64_t cum = 0;
-                int d = 255;
-                for (; d > 0; --d) {
-                    if (cum + hist[d] >= need) break;
-                    cum += hist[d];
-                }
-                s_prefix = prefix | ((uint64_t)d << shift);
-                s_need = need - cum;
+                s_br[0] = 0;
+                s_br[1] = ~0ull;
             }
             __syncthreads();
-            prefix = s_prefix;
-            need = s_need;
-            mask |= 255ull << shift;
+            // sample ranks k_s -+ (4 sqrt(k_s) + 16) around the threshold's
+            const double ks = (double)take * SS_SAMPLE / (double)navail, dl = 4.0 * sqrt(ks) + 16.0;
+            const int64_t c_hi = (int64_t)floor(ks - dl), c_lo = (int64_t)ceil(ks + dl);
+            const uint32_t h0 = s_h[2 * tid], h1 = s_h[2 * tid + 1];
+            uint64_t tot;
+            const int64_t below = (int64_t)ss_scan(h0 + h1, s_w, tot);
+            const int64_t suf1 = (int64_t)tot - below - h0, suf0 = (int64_t)tot - below;   // in bins >= 2 tid + 1, >= 2 tid
+            auto edge = [&](int bin) { return mn + (double)bin / sc; };
+            if (sc > 0.0 && mn >= 0.0) {
+                // upper end: the bin where the count from the top reaches c_hi; lower end likewise c_lo
+                const int64_t suf2 = suf1 - h1;
+                if (c_hi >= 1) {
+                    if (suf2 < c_hi && c_hi <= suf1) s_br[1] = d2u(edge(2 * tid + 2));
+                    if (suf1 < c_hi && c_hi <= suf0) s_br[1] = d2u(edge(2 * tid + 1));
+                }
+                if (c_lo <= SS_SAMPLE) {
+                    if (suf2 < c_lo && c_lo <= suf1) s_br[0] = d2u(edge(2 * tid + 1));
+                    if (suf1 < c_lo && c_lo <= suf0) s_br[0] = d2u(edge(2 * tid));
+                }
+            }
             __syncthreads();
+            blo = s_br[0];
+            bhi = s_br[1];
+        } else {
+            __syncthreads();
+        }
+        // count the keys above the bracket, list those inside it
+        uint32_t nab = 0;
+        // (the next round's keys load while this one's are sorted out; one
+        // list append per wave and round)
+        constexpr int64_t ROUND = (int64_t)SS_THREADS * SS_PER;
+        uint64_t k[SS_PER];
+        auto load = [&](int64_t u0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < SS_PER; ++j) k[j] = ka[min(u0 + tid + (int64_t)SS_THREADS * j, navail - 1)];
+        };
+        load(0);
+        for (int64_t u0 = 0; u0 < navail; u0 += ROUND) {
+            uint64_t c[SS_PER];
+#pragma unroll
+            for (int j = 0; j < SS_PER; ++j) c[j] = k[j];
+            if (u0 + ROUND < navail) load(u0 + ROUND);
+            uint64_t bal[SS_PER];
+            uint32_t found = 0;
+#pragma unroll
+            for (int j = 0; j < SS_PER; ++j) {
+                const bool live = u0 + tid + (int64_t)SS_THREADS * j < navail;
+                nab += live && c[j] > bhi;
+                bal[j] = __ballot(live && c[j] >= blo && c[j] <= bhi);
+                found += __popcll(bal[j]);
+            }
+            if (found == 0) continue;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&s_cnt[1], found);
+            at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+            for (int j = 0; j < SS_PER; ++j) {
+                const uint32_t p = at + __popcll(bal[j] & ((1ull << lane) - 1ull));
+                if (((bal[j] >> lane) & 1) && p < SS_LIST) s_list[p] = c[j];
+                at += __popcll(bal[j]);
+            }
+        }
+        for (int o = 32; o > 0; o >>= 1) nab += __shfl_xor(nab, o);
+        if (lane == 0 && nab) atomicAdd(&s_cnt[0], nab);
+        __syncthreads();
+        const int64_t above = s_cnt[0], inside = s_cnt[1];
+        if (inside <= SS_LIST && above < take && take <= above + inside) {
+            need = take - above;
+            // the digits start at the first bit in which the bracket's ends differ
+            const uint64_t diff = blo ^ bhi;
+            const int top = diff ? 63 - __clzll((long long)diff) : 0;
+            const int shift = top < 7 ? 0 : top - 7;
+            const uint64_t mask = shift + 8 >= 64 ? 0ull : ~0ull << (shift + 8);
+            thr = ss_radix([&](int64_t i) { return s_list[i]; }, inside, blo & mask, mask, shift, need, s_h, &s_d,
+                           &s_above, &s_br[0]);
+        } else {
+            thr = ss_radix([&](int64_t i) { return ka[i]; }, navail, 0ull, 0ull, 56, need, s_h, &s_d, &s_above,
+                           &s_br[0]);
         }
     }
-    // ordered pass: sinks, keys above the threshold, and the first `need` rows equal to it
-    const bool all = take == navail;
+    // ordered output: sinks, keys above the threshold, and the first `need` rows equal to it
+    uint64_t* s_gt = s_list;               // per 64 rows: rows certainly in
+    uint64_t* s_eq = s_list + SS_WORDS;    // rows equal to the threshold
     int64_t base = 0, eq_seen = 0;
-    for (int64_t u0 = 0; u0 < a.n; u0 += SS_THREADS) {
-        const int64_t u = u0 + tid;
-        bool in = false, eq = false;
-        if (u < a.n) {
-            if (u < lo) {
-                in = true;
-            } else if (all) {
-                in = true;
-            } else if (take > 0) {
-                const uint64_t k = key[u];
-                in = k > prefix;
-                eq = k == prefix;
+    constexpr int64_t SEG = 64ll * SS_WORDS;
+    __syncthreads();
+    for (int64_t g0 = 0; g0 < a.n; g0 += SEG) {
+        const int nw = (int)((min(a.n - g0, SEG) + 63) / 64);
+        uint64_t k[SS_PER];
+        auto load = [&](int w0) __attribute__((always_inline)) {
+            if (take == 0 || all) return;   // no key decides
+#pragma unroll
+            for (int j = 0; j < SS_PER; ++j) k[j] = key[min(g0 + (int64_t)64 * (w0 + SS_WAVES * j) + lane, a.n - 1)];
+        };
+        load(wave);
+        for (int w0 = wave; w0 < nw; w0 += SS_WAVES * SS_PER) {
+            uint64_t c[SS_PER];
+#pragma unroll
+            for (int j = 0; j < SS_PER; ++j) c[j] = k[j];
+            if (w0 + SS_WAVES * SS_PER < nw) load(w0 + SS_WAVES * SS_PER);
+#pragma unroll
+            for (int j = 0; j < SS_PER; ++j) {
+                const int w = w0 + SS_WAVES * j;
+                const int64_t u = g0 + 64ll * w + lane;
+                const bool cand = u >= lo && u < a.n && take > 0;
+                const bool in = u < a.n && (u < lo || (cand && (all || c[j] > thr)));
+                const uint64_t gt = __ballot(in), eq = __ballot(cand && !all && c[j] == thr);
+                if (w < nw && lane == 0) {
+                    s_gt[w] = gt;
+                    s_eq[w] = eq;
+                }
             }
         }
-        int neq = 0;
-        const int er = block_rank(eq, s_w, tid, &neq);
-        if (eq && eq_seen + er < need) in = true;
-        eq_seen += neq;
-        int nin = 0;
-        const int r = block_rank(in, s_w, tid, &nin);
-        if (in) out[base + r] = (int32_t)u;
-        base += nin;
+        __syncthreads();
+        // words 2 tid and 2 tid + 1: rows in, and equal rows, before them
+        uint64_t cnt = 0;
+        uint64_t gt[2], eq[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int w = 2 * tid + j;
+            gt[j] = w < nw ? s_gt[w] : 0;
+            eq[j] = w < nw ? s_eq[w] : 0;
+            cnt += (uint64_t)__popcll(gt[j]) | ((uint64_t)__popcll(eq[j]) << 32);
+        }
+        uint64_t tot;
+        const uint64_t before = ss_scan(cnt, s_w, tot);
+        int64_t ng = (int64_t)(before & 0xFFFFFFFFull), ne = eq_seen + (int64_t)(before >> 32);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            uint64_t bits = gt[j] | eq[j];
+            int64_t pos = base + ng + min(ne, need) - min(eq_seen, need);
+            const int64_t u0 = g0 + 64ll * (2 * tid + j);
+            while (bits) {
+                const int e = __ffsll((unsigned long long)bits) - 1;
+                bits &= bits - 1;
+                if ((gt[j] >> e) & 1) {
+                    out[pos++] = (int32_t)(u0 + e);
+                } else if (ne++ < need) {
+                    out[pos++] = (int32_t)(u0 + e);
+                }
+            }
+            ng += __popcll(gt[j]);
+            ne = eq_seen + (int64_t)(before >> 32) + __popcll(eq[0]);   // before word 2 tid + 1
+        }
+        const int64_t eq_after = eq_seen + (int64_t)(tot >> 32);
+        base += (int64_t)(tot & 0xFFFFFFFFull) + min(eq_after, need) - min(eq_seen, need);
+        eq_seen = eq_after;
+        __syncthreads();
     }
 }
 
