@@ -709,18 +709,21 @@ int vkv_step_run(vkv_ctx* ctx, const vkv_step* st, void* ws, size_t ws_bytes, in
 static hipError_t run_row_max(const vkv_step* st, const int32_t* rows, int64_t nrows, int all_archive, int add_recent,
                               double* smax, int32_t* argmax, hipStream_t s, char* ws = nullptr) {
     RowMaxArgs a{};
-    // with a workspace: row ranges in parallel, about one workgroup per CU in
-    // all (a workgroup holds 8 head groups of 16), at least 64 rows each
-    a.nsplit = 1;
+    // row ranges in parallel, about one workgroup per CU in all (a workgroup
+    // holds 8 head groups of 16), at least 64 rows each.  With a workspace the
+    // ranges' maxima go through it (at most RM_MAX_SPLIT of them); without one
+    // they are merged into the outputs, and a range is at least 256 rows, so
+    // that the merge stays small beside it.
+    const int64_t N = (all_archive ? st->T - st->W : nrows) + (add_recent ? st->W : 0);
+    const int64_t blocks = ((st->H + 127) / 128) * st->B;
+    const int64_t want = std::max<int64_t>(1, (256 + blocks - 1) / std::max<int64_t>(blocks, 1));
     if (ws) {
-        const int64_t N = (all_archive ? st->T - st->W : nrows) + (add_recent ? st->W : 0);
-        const int64_t blocks = ((st->H + 127) / 128) * st->B;
-        int64_t ns = std::max<int64_t>(1, (256 + blocks - 1) / std::max<int64_t>(blocks, 1));
-        ns = std::min<int64_t>({ns, (int64_t)RM_MAX_SPLIT, std::max<int64_t>(1, N / 64)});
-        a.nsplit = (int)ns;
+        a.nsplit = (int)std::min<int64_t>({want, (int64_t)RM_MAX_SPLIT, std::max<int64_t>(1, N / 64)});
         const WsLayout L = layout(st, 0, 0);
         a.part_v = reinterpret_cast<double*>(ws + L.rmx);
         a.part_u = reinterpret_cast<int32_t*>(ws + L.rmx + (size_t)(st->B * st->H * RM_MAX_SPLIT * 8));
+    } else {
+        a.nsplit = (int)std::min<int64_t>(want, std::max<int64_t>(1, N / 256));
     }
     a.q_lat = st->q_lat;
     a.q_rope = st->q_rope;

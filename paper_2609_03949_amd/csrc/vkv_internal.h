@@ -249,8 +249,8 @@ struct RowMaxArgs {
     int B, H;
     double* smax;           // [B,H]
     int32_t* argmax;        // [B,H]
-    int nsplit;             // row ranges scanned in parallel (1: no scratch needed)
-    double* part_v;         // [B,H,nsplit] per-range maxima (nsplit > 1)
+    int nsplit;             // row ranges scanned in parallel
+    double* part_v;         // [B,H,nsplit] per-range maxima (null: the ranges are merged into smax / argmax)
     int32_t* part_u;        // [B,H,nsplit] their rows
 };
 constexpr int RM_MAX_SPLIT = 16;
