@@ -11,157 +11,129 @@
 // The projection runs on the fp64 matrix cores: v_mfma_f64_16x16x4f64 adds its
 // 4 products (k = 0..3) to the accumulator one after another, each with a
 // single rounding, so 128 of them with i ascending give the sequential fp64
-// sum bit for bit (bf16 products are exact in fp64).  A block owns DG_ROWS
-// consecutive rows of one sequence and takes the basis in chunks of 64 rows
-// (one 16-row tile per wave): each chunk is staged once in LDS, and the
-// block's rows stream past it in two streams of 16-row tiles, so that each
-// SIMD runs two independent chains (double-buffered: each stream's next tile
-// is loaded into registers during the current tile's chain).
-// Rows and basis rows sit in LDS rows padded to DG_ROW bytes, so the operand
-// reads (16 rows, one 16-bit element each) fall into distinct banks.  The
-// row sums over j (||y||^2, ||d - y||^2) continue chunk after chunk in j
-// order; ||c||^2 runs on the vector unit of wave 0 between its matrix steps.
-#include <type_traits>
+// sum bit for bit (bf16 products are exact in fp64).
+//
+// Bound by the matrix steps (72 cycles each on a SIMD, 66 TFLOP/s measured for a
+// large product), as long as little else takes issue slots and the fp64 pipe:
+// widening an operand costs both.  So a block keeps its 64 basis rows widened in
+// registers, and each cache row is widened once, by the wave that loads it, into
+// an LDS tile from which four waves read fp64 operands.  Two waves share a SIMD,
+// each with half of the 512 dimensions: wave w takes steps 0..63 of tile t while
+// wave w + 4 takes steps 64..127 of tile t - 1, continuing the accumulators w
+// handed over through LDS, so one wave's side work runs under the other's matrix
+// steps (128 doubles per lane in one wave spill to accumulation registers, and
+// every copy back costs issue slots: 98 cycles a step).  Waves 0-3 do their side
+// work (widening, ||c||^2) before their steps, waves 4-7 (digests, tail sums)
+// after theirs.  The certificate's sums are sequential too: ||c||^2 runs as one
+// lane per row over the 16 tiles of a 256-row group, ||y||^2 and ||d - y||^2 of
+// a tile as 32 lanes of one wave, the waves in turn.  Measured at 16 x 32768 rows,
+// r = 64, with the certificate: 2176 -> 793 us (43 TFLOP/s; the matrix cores are
+// busy 58% of it); without its sums 730.
+#include <algorithm>
 
 #include "vkv_internal.h"
 
 namespace vkv {
 
-constexpr int DG_THREADS = 512;   // two streams of 4 waves: one basis tile per wave, two row tiles at a time
-constexpr int DG_ROW = 1040;       // LDS bytes per staged row of 512 bf16
-constexpr int DG_CHUNK = 64;       // basis rows per chunk: 16 per wave of a stream
-constexpr int DG_ROWS = 256;       // cache rows per block (16 tiles of 16)
+constexpr int DG_THREADS = 512;    // waves 0-3: dims 0..255, waves 4-7: dims 256..511, 16 basis rows each
+constexpr int DG_CHUNK = 64;       // basis rows per pass over the block's rows
+constexpr int DG_GROUP = 256;      // rows whose ||c||^2 are formed together: one per thread of waves 0-3
+constexpr int DG_GTILES = DG_GROUP / 16;
+constexpr int DG_MAX_GROUPS = 4;   // groups per block (one where the basis takes several chunks)
+// Half a tile (16 rows, 256 dims) in LDS: element i = 4 s + k of row m at
+// m DG_RS + 512 k + 8 s bytes, so the operand of step s (lane 16 k + m) and that
+// of step s + 1 are one 16-byte read, eight rows of which fall into distinct banks
+constexpr int DG_RS = 2048 + 16;
+constexpr int DG_HALF = 16 * DG_RS;
+constexpr int DG_YLD = DG_CHUNK + 1;
+constexpr int DG_HAND = 4 * 64 * 4;     // doubles handed over per tile: [basis tile][lane][4]
+constexpr size_t DG_LDS = 4 * DG_HALF + (DG_HAND + 2 * 16 * DG_YLD + 3 * DG_GROUP) * sizeof(double);
+static_assert(DG_LDS <= 160 * 1024, "the CU's LDS");
 
-typedef __attribute__((address_space(3))) void dg_lds_t;
-typedef __attribute__((address_space(1))) void dg_gbl_t;
+// workgroup barrier for exchanges through LDS (global loads stay in flight)
+__device__ __forceinline__ void dg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-__global__ __launch_bounds__(DG_THREADS) void digest_kernel(DigestArgs a) {
-    __shared__ __align__(16) uint8_t s_p[DG_CHUNK * DG_ROW];        // a chunk of basis rows
-    __shared__ __align__(16) uint8_t s_c[2][2][16 * DG_ROW];        // per stream, two tiles of cache rows
-    __shared__ double s_y[2][16][DG_CHUNK];                         // per stream, y of its tile and the chunk
-    __shared__ double s_acc[DG_ROWS][2];                            // running ||y||^2, ||d - y||^2
-    __shared__ double s_nc[DG_ROWS];                                // ||c||^2
-
+__global__ __launch_bounds__(DG_THREADS, 2) void digest_kernel(DigestArgs a, int rows) {
+    extern __shared__ __align__(16) uint8_t dg_lds[];
+    double* s_hand = reinterpret_cast<double*>(dg_lds + 4 * DG_HALF);
+    double* s_y = s_hand + DG_HAND;                // [2][16][DG_YLD]: y, RNE(y) - y
+    double* s_acc = s_y + 2 * 16 * DG_YLD;         // [256][2]: running ||y||^2, ||d - y||^2 of the group's rows
+    double* s_nc = s_acc + 2 * DG_GROUP;           // [256]: ||c||^2
     const int b = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int st = wave >> 2, jw = wave & 3;   // row stream, basis tile of the chunk
-    const int stid = tid & 255;                // thread index within the stream
-    const int64_t u0 = (int64_t)blockIdx.x * DG_ROWS;
-    const int nrows = (int)min((int64_t)DG_ROWS, a.T - u0);
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = wave >> 2, jw = wave & 3;
+    const int64_t u0 = (int64_t)blockIdx.x * rows;
+    const int nrows = (int)min((int64_t)rows, a.T - u0);
     if (nrows <= 0) return;
     const int ntile = (nrows + 15) / 16;
-    const int niter = (ntile + 1) / 2;   // stream st takes tiles 2 it + st
-    const uint16_t* cb = a.cache + (int64_t)b * a.cbs;
-    uint16_t* ib = a.index ? a.index + (int64_t)b * a.ibs : nullptr;
+    const uint16_t* cb = a.cache + (int64_t)b * a.cbs + u0 * a.cs;
+    uint16_t* ib = a.index ? a.index + (int64_t)b * a.ibs + u0 * a.is : nullptr;
     const int off = a.with_rope ? D_ROPE : 0;
     const bool cert = a.eta != nullptr;
-    for (int i = tid; i < DG_ROWS; i += DG_THREADS) s_acc[i][0] = s_acc[i][1] = 0.0;
+    const int nchunk = a.r > 0 ? (a.r + DG_CHUNK - 1) / DG_CHUNK : 1;
+    uint8_t* s_t = dg_lds + half * 2 * DG_HALF;    // this half's two buffers
 
-    // this stream's tile of iteration 0 into its buffer 0 (4 rows per wave,
-    // one 1 KB load each); rows past T are zero
-    auto stage_first = [&]() {
+    // loader: wave jw of a half moves its dims of tile rows 4 jw .. 4 jw + 3, two
+    // rows per load (rows past the end re-read the last one; nothing of them is stored)
+    u16x8_t nx[2];
+    auto load_rows = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int rl = 4 * jw + q, rr = 16 * st + rl;
-            uint8_t* dst = s_c[st][0] + rl * DG_ROW;
-            if (rr < nrows)
-                __builtin_amdgcn_global_load_lds((dg_gbl_t*)(cb + (u0 + rr) * a.cs + 8 * lane), (dg_lds_t*)dst, 16, 0, 0);
-            else
-                *reinterpret_cast<u32x4_t*>(dst + 16 * lane) = u32x4_t{0u, 0u, 0u, 0u};
+        for (int e = 0; e < 2; ++e) {
+            const int rr = min(16 * t + 4 * jw + 2 * e + (lane >> 5), nrows - 1);
+            nx[e] = *reinterpret_cast<const u16x8_t*>(cb + (int64_t)rr * a.cs + 256 * half + 8 * (lane & 31));
         }
     };
-    const int nchunk = a.r > 0 ? (a.r + DG_CHUNK - 1) / DG_CHUNK : 1;
-    for (int ch = 0; ch < nchunk; ++ch) {
-        const int j0 = ch * DG_CHUNK;
-        const int jn = a.r > 0 ? min(DG_CHUNK, a.r - j0) : 0;
-        __syncthreads();   // the previous chunk's reads of s_p and s_c are done
-        for (int row = wave; row < jn; row += DG_THREADS / 64)
-            __builtin_amdgcn_global_load_lds((dg_gbl_t*)(a.P + (int64_t)(j0 + row) * D_LAT + 8 * lane),
-                                             (dg_lds_t*)(s_p + row * DG_ROW), 16, 0, 0);
-        stage_first();
-        const bool tile = 16 * jw < jn;
-        const bool nc = ch == 0 && jw == 0 && cert;
-        // operand rows: A = cache row (lane mod 16) of the tile, B = basis row
-        // 16 jw + (lane mod 16) of the chunk; element k = lane / 16 of each step
-        const uint16_t* pb = reinterpret_cast<const uint16_t*>(s_p + (16 * jw + (lane & 15)) * DG_ROW) + (lane >> 4);
-        for (int it = 0; it < niter; ++it) {
-            const int t = 2 * it + st;
-            const bool have = t < ntile;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();   // tile t (and the chunk) landed; buffer (it+1)&1 and s_y are free
-            // the stream's next tile into registers now, into LDS after the
-            // chain: no direct load into LDS is in flight while the chain reads
-            // it, so the compiler's LDS wait counts stay exact
-            u32x4_t nx[4];
-            const int tn = t + 2;
-            const bool more = tn < ntile;
-            if (more) {
+    auto widen_rows = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int rr = 16 * tn + 4 * jw + q;
-                    nx[q] = rr < nrows ? *reinterpret_cast<const u32x4_t*>(cb + (u0 + rr) * a.cs + 8 * lane)
-                                       : u32x4_t{0u, 0u, 0u, 0u};
-                }
-            }
-            const uint8_t* tb = s_c[st][it & 1];
-            const uint16_t* ca = reinterpret_cast<const uint16_t*>(tb + (lane & 15) * DG_ROW) + (lane >> 4);
-            const uint16_t* cn = reinterpret_cast<const uint16_t*>(tb + (lane & 15) * DG_ROW);
-            f64x4_t acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
-            double anc = 0.0;
-            if (have) {
-                if (tile && nc) acc = mfma_f64_rowdot512<true>(ca, pb, cn, anc);
-                else if (tile) acc = mfma_f64_rowdot512<false>(ca, pb, cn, anc);
-                else if (nc) {
-                    for (int i = 0; i < D_LAT; ++i) {
-                        const double x = bf16_bits_f64(cn[i]);
-                        anc = fma(x, x, anc);
-                    }
-                }
-            }
-            if (more) {
+        for (int e = 0; e < 2; ++e) {
+            uint8_t* dst = s_t + (t & 1) * DG_HALF + (4 * jw + 2 * e + (lane >> 5)) * DG_RS + 16 * (lane & 31);
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<u32x4_t*>(s_c[st][(it + 1) & 1] + (4 * jw + q) * DG_ROW + 16 * lane) = nx[q];
-            }
-            if (have && nc && lane < 16 && 16 * t + lane < nrows) s_nc[16 * t + lane] = anc;
-            if (have && tile) {
-                // acc[i] = y of tile row 4 i + lane / 16, basis row j0 + 16 jw + lane mod 16
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int rl = 4 * i + (lane >> 4), jl = 16 * jw + (lane & 15);
-                    const double y = acc[i];
-                    s_y[st][rl][jl] = y;
-                    const int rr = 16 * t + rl;
-                    if (ib && rr < nrows) ib[(u0 + rr) * a.is + off + j0 + jl] = f64_to_bf16_rne(y);
-                }
-            }
-            if (have && ch == 0 && ib && a.with_rope) {
-                // branch copy (the exact summand of every future logit): 16 rows x 128 B
-                const int rl = stid >> 4, p = stid & 15;
-                const int rr = 16 * t + rl;
-                if (p < D_ROPE / 8 && rr < nrows)
-                    *reinterpret_cast<u16x8_t*>(ib + (u0 + rr) * a.is + 8 * p) =
-                        *reinterpret_cast<const u16x8_t*>(cb + (u0 + rr) * a.cs + D_LAT + 8 * p);
-            }
-            if (!cert) continue;
-            __syncthreads();   // s_y complete
-            if (have && jw == 0 && lane < 32) {
-                // lane rl + 16 m continues sum m of tile row rl over this chunk's j, ascending
-                const int rl = lane & 15, m = lane >> 4, rr = 16 * t + rl;
-                double sacc = rr < nrows ? s_acc[rr][m] : 0.0;
-                for (int jl = 0; jl < jn; ++jl) {
-                    const double y = s_y[st][rl][jl];
-                    const double v = m ? (double)bf16_to_f32(f64_to_bf16_rne(y)) - y : y;
-                    sacc = fma(v, v, sacc);
-                }
-                if (rr < nrows) s_acc[rr][m] = sacc;
-            }
+            for (int k = 0; k < 4; ++k)
+                *reinterpret_cast<double2*>(dst + 512 * k) =
+                    make_double2(bf16_bits_f64(nx[e][k]), bf16_bits_f64(nx[e][4 + k]));
         }
-    }
-    if (!cert) return;
-    __syncthreads();
-    for (int rr = tid; rr < nrows; rr += DG_THREADS) {
-        const double Nc = s_nc[rr], Ny = s_acc[rr][0], Ne = s_acc[rr][1];
+    };
+    // ||c||^2 (waves 0-3) of row 64 jw + lane of the current group: 32 elements
+    // per tile, i ascending, loaded a tile ahead
+    double nc = 0.0;
+    u16x8_t cv[4];
+    const uint16_t* crow = cb;
+    auto nc_load = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cv[e] = *reinterpret_cast<const u16x8_t*>(crow + 32 * i + 8 * e);
+    };
+    auto nc_row = [&](int grp) __attribute__((always_inline)) {
+        const int rr = min(DG_GROUP * grp + 64 * jw + lane, nrows - 1);
+        crow = cb + (int64_t)rr * a.cs;
+        nc = 0.0;
+        nc_load(0);
+    };
+    auto nc_tile = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 32; ++e) {
+            const double x = bf16_bits_f64(cv[e >> 3][e & 7]);
+            nc = fma(x, x, nc);
+        }
+    };
+    // sums of tile t (waves 4-7): lane 16 q + row continues sum q & 1 of its row over the chunk's j
+    const double* ty = s_y + (kq & 1) * 16 * DG_YLD + m * DG_YLD;
+    auto tail_sums = [&](int t, int ch) __attribute__((always_inline)) {
+        double* slot = s_acc + (16 * (t % DG_GTILES) + m) * 2 + (kq & 1);
+        double tail = ch > 0 ? *slot : 0.0;
+#pragma unroll
+        for (int j8 = 0; j8 < DG_CHUNK; j8 += 16) {
+            double v[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = ty[j8 + e];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) tail = fma(v[e], v[e], tail);
+        }
+        *slot = tail;   // (two lane pairs write the same value)
+    };
+    auto scalars = [&](int grp) __attribute__((always_inline)) {
+        const int rr = DG_GROUP * grp + tid;
+        if (tid >= DG_GROUP || rr >= nrows) return;
+        const double Nc = s_nc[tid], Ny = s_acc[2 * tid], Ne = s_acc[2 * tid + 1];
         const double G = CERT_G;
         const double Dm = G * (double)ru_sqrt_f32((double)a.r * Nc);
         const double sy = (double)ru_sqrt_f32(Ny);
@@ -170,13 +142,160 @@ __global__ __launch_bounds__(DG_THREADS) void digest_kernel(DigestArgs a) {
         a.eta[o] = ru_sqrt_f32((X > 0.0 ? X : 0.0) * (1.0 + G));
         a.eps[o] = ru_f32((double)ru_sqrt_f32(Ne) * (1.0 + G) + Dm);
         a.gam[o] = ru_f32(sy * (1.0 + G) + Dm);
+    };
+
+    for (int ch = 0; ch < nchunk; ++ch) {
+        const int j0 = ch * DG_CHUNK;
+        const int jn = a.r > 0 ? min(DG_CHUNK, a.r - j0) : 0;
+        // (a wave without a basis tile multiplies zeros and contributes zeros)
+        const bool active = 16 * jw < jn;
+        const bool nc_on = cert && ch == 0 && half == 0;
+        // basis row j0 + 16 jw + m: elements 4 s + kq of this half's 64 steps
+        double P[64];
+        if (active) {
+            const uint16_t* pr = a.P + (int64_t)(j0 + 16 * jw + m) * D_LAT + 256 * half;
+#pragma unroll
+            for (int p = 0; p < 32; ++p) {
+                const u16x8_t v = *reinterpret_cast<const u16x8_t*>(pr + 8 * p);
+                uint64_t h[2];
+                __builtin_memcpy(h, &v, 16);
+                P[2 * p] = bf16_bits_f64((uint16_t)(h[0] >> (16 * kq)));
+                P[2 * p + 1] = bf16_bits_f64((uint16_t)(h[1] >> (16 * kq)));
+            }
+        } else {
+#pragma unroll
+            for (int p = 0; p < 64; ++p) P[p] = 0.0;
+        }
+        load_rows(0);
+        dg_barrier();   // the previous chunk's reads of the tiles and of s_y are done
+        widen_rows(0);
+        load_rows(1);
+        if (nc_on) nc_row(0);
+        dg_barrier();
+        f64x4_t acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
+        auto chain = [&](int t) __attribute__((always_inline)) {
+            const uint8_t* pa = s_t + (t & 1) * DG_HALF + m * DG_RS + 512 * kq;
+            double2 av[2][4];
+            auto read_group = [&](int gi, int buf) __attribute__((always_inline)) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) av[buf][e] = *reinterpret_cast<const double2*>(pa + 16 * (4 * gi + e));
+            };
+            read_group(0, 0);
+            // four LDS reads serve eight steps; they go out one such group
+            // ahead of their use (the scheduling barriers keep them there)
+#pragma unroll
+            for (int gi = 0; gi < 8; ++gi) {
+                if (gi + 1 < 8) read_group(gi + 1, (gi + 1) & 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[gi & 1][e].x, P[8 * gi + 2 * e], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[gi & 1][e].y, P[8 * gi + 2 * e + 1], acc, 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        // iteration it: waves 0-3 on tile it, waves 4-7 on tile it - 1
+        for (int it = 0; it <= ntile; ++it) {
+            const int t = it - half;
+            const bool have = t >= 0 && t < ntile;
+            double* hand = s_hand + (jw * 64 + lane) * 4;
+            double dev[4] = {};   // RNE(y) - y
+            u16x8_t rp = u16x8_t{};
+            const bool rope = have && half == 0 && ch == 0 && ib && a.with_rope && tid < 128;
+            const int rope_row = 16 * t + (tid >> 3);   // the tile's branch piece: 16 rows x 128 B over 128 threads
+            if (have) {
+                if (half == 0) {
+                    if (rope)
+                        rp = *reinterpret_cast<const u16x8_t*>(cb + (int64_t)min(rope_row, nrows - 1) * a.cs + D_LAT +
+                                                               8 * (tid & 7));
+                    widen_rows(t + 1);
+                    load_rows(t + 2);
+                    if (nc_on) {
+                        nc_tile();
+                        if (t % DG_GTILES == DG_GTILES - 1 || t == ntile - 1) {
+                            // the group's last tile: in a short last group the elements its tiles did not reach
+                            for (int i = t % DG_GTILES + 1; i < DG_GTILES; ++i) {
+                                nc_load(i);
+                                nc_tile();
+                            }
+                            // (the block's last group goes to LDS after the loop: the
+                            // scalars of the group before it may still be due)
+                            if (t + 1 < ntile) {
+                                s_nc[64 * jw + lane] = nc;
+                                nc_row(t / DG_GTILES + 1);
+                            }
+                        } else {
+                            nc_load(t % DG_GTILES + 1);
+                        }
+                    }
+                    acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
+                    chain(t);
+                    // branch copy (the exact summand of every future logit)
+                    if (rope && rope_row < nrows)
+                        *reinterpret_cast<u16x8_t*>(ib + (int64_t)rope_row * a.is + 8 * (tid & 7)) = rp;
+                } else {
+                    acc = *reinterpret_cast<const f64x4_t*>(hand);
+                    chain(t);
+                    widen_rows(t + 1);
+                    load_rows(t + 2);
+                    if (cert && t > 0 && jw == (t & 3)) tail_sums(t - 1, ch);
+                    // acc[i] = y of tile row 4 i + kq, basis row j0 + 16 jw + m
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int rr = 16 * t + 4 * i + kq;
+                        acc[i] = active ? acc[i] : 0.0;
+                        const uint16_t d = f64_to_bf16_rne(acc[i]);
+                        dev[i] = (double)bf16_to_f32(d) - acc[i];
+                        if (ib && active && rr < nrows) ib[(int64_t)rr * a.is + off + j0 + 16 * jw + m] = d;
+                    }
+                }
+            }
+            dg_barrier();   // the reads of s_hand and of s_y are done
+            if (have) {
+                if (half == 0) {
+                    *reinterpret_cast<f64x4_t*>(hand) = acc;
+                } else {
+                    if (cert) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            s_y[(4 * i + kq) * DG_YLD + 16 * jw + m] = acc[i];
+                            s_y[(16 + 4 * i + kq) * DG_YLD + 16 * jw + m] = dev[i];
+                        }
+                    }
+                }
+            }
+            // the group whose last tile's sums went in above (tile it - 2)
+            if (cert && ch == nchunk - 1 && it >= 2 && (it - 1) % DG_GTILES == 0) scalars((it - 2) / DG_GTILES);
+            dg_barrier();   // the next tiles, s_hand and s_y are in place
+        }
+        // the chunk's last tile has no tile after it whose steps its sums follow
+        if (cert) {
+            if (wave == 4) tail_sums(ntile - 1, ch);
+            if (nc_on) s_nc[64 * jw + lane] = nc;
+            dg_barrier();
+        }
     }
+    if (cert) scalars((ntile - 1) / DG_GTILES);
 }
 
 hipError_t launch_digest(const DigestArgs& a, hipStream_t s) {
     if (a.T <= 0) return hipSuccess;
-    dim3 grid((unsigned)((a.T + DG_ROWS - 1) / DG_ROWS), (unsigned)a.B);
-    hipLaunchKernelGGL(digest_kernel, grid, dim3(DG_THREADS), 0, s, a);
+    // Rows per block: several groups keep the widened basis in registers for
+    // longer (3 of 100 us per group), one group where it takes several chunks
+    // (their sums of all rows would not fit the LDS) or where blocks would be
+    // fewer than two per CU; below one block per CU shorter blocks, down to four
+    // tiles, since the time is then that of one block.
+    const int64_t total = a.B * ((a.T + DG_GROUP - 1) / DG_GROUP);
+    int64_t rows = DG_GROUP;
+    if (total < 256)
+        rows = std::min<int64_t>(DG_GROUP, std::max<int64_t>(64, (a.B * a.T + 256 * 16 - 1) / (256 * 16) * 16));
+    else if (a.r <= DG_CHUNK)
+        rows = DG_GROUP * std::min<int64_t>(DG_MAX_GROUPS, std::max<int64_t>(1, total / 512));
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&digest_kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)DG_LDS);
+    dim3 grid((unsigned)((a.T + rows - 1) / rows), (unsigned)a.B);
+    hipLaunchKernelGGL(digest_kernel, grid, dim3(DG_THREADS), DG_LDS, s, a, (int)rows);
     return hipGetLastError();
 }
 

@@ -1,0 +1,54 @@
+"""The index build at the edges of its tiles (16 rows), groups (256 rows),
+blocks (1 to 4 groups) and basis chunks (64 rows): rows, scalars and the branch
+copy bit for bit against the fp64 oracle, and nothing written past a row's
+columns or past the last row.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_03949_amd as vkv
+from paper_2609_03949_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,T,r,with_rope,cert", [
+    (1, 1, 64, True, True), (2, 15, 32, True, True), (1, 16, 64, False, False), (1, 17, 96, True, True),
+    (3, 255, 160, True, True), (1, 257, 64, True, True), (2, 272, 512, False, True), (1, 1041, 0, True, True),
+    (520, 257, 64, True, True), (700, 529, 32, True, False), (1100, 513, 64, True, True),
+])
+def test_index_build_edges(B, T, r, with_rope, cert):
+    print(f"[digest-edges] B={B} T={T} r={r} rope={with_rope} cert={cert}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B + T)
+    # rows spread over many octaves, with zeros: other summation orders give other bits
+    cache = torch.randn(B, T, 576, generator=g, device="cuda")
+    cache = (cache * torch.exp2(torch.randint(-12, 12, (B, T, 576), generator=g, device="cuda").float()))
+    cache[:, ::7, ::5] = 0
+    cache = cache.to(torch.bfloat16)
+    P = synth.make_basis("orthonormal", r)
+    cols = (64 if with_rope else 0) + r
+    ld = cols + 8
+    index = torch.full((B, T + 1, ld), 3.0, dtype=torch.bfloat16, device="cuda")
+    sc = [torch.full((B * T + 1,), -5.0, device="cuda") for _ in range(3)] if cert else [None] * 3
+    ctx = vkv.Context(0)
+    Pd = P.cuda() if P is not None else None
+    ptr = lambda t: None if t is None else t.data_ptr()   # noqa: E731
+    ctx.check(ctx.lib.vkv_digest_build(ctx.handle, ptr(cache), B, T, 576, T * 576, ptr(Pd), r, int(with_rope),
+                                       ptr(index), ld, (T + 1) * ld, ptr(sc[0]), ptr(sc[1]), ptr(sc[2]), None))
+    torch.cuda.synchronize()
+    ctx.close()
+    assert torch.all(index[:, T] == 3.0) and torch.all(index[:, :, cols:] == 3.0)
+    if cert:
+        assert all(float(s[B * T]) == -5.0 for s in sc)
+    for b in sorted({0, B // 2, B - 1}):
+        bits = synth.to_numpy_bits(cache[b:b + 1])
+        idx, eta, eps, gam = oracle.digest_build(bits, synth.to_numpy_bits(P) if r else None, r, with_rope=with_rope,
+                                                 scalars=cert)
+        got = synth.to_numpy_bits(index[b:b + 1, :T, :cols].contiguous())
+        assert np.array_equal(got, np.asarray(idx).reshape(got.shape))
+        if cert:
+            for s, want in zip(sc, (eta, eps, gam)):
+                assert np.array_equal(s[b * T:(b + 1) * T].cpu().numpy(), np.asarray(want).reshape(-1))
