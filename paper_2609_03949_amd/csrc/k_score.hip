@@ -233,17 +233,6 @@ __device__ __forceinline__ void store_head_maxima(const ScoreArgs& a, int b, int
     }
 }
 
-// maxima of (a, n, e) over the head scalars staged in LDS
-__device__ __forceinline__ void staged_head_maxima(const float4* s_hs, int n, float& amax, float& nmax, float& emax) {
-    amax = nmax = emax = 0.f;
-    for (int i = 0; i < n; ++i) {
-        const float4 v = s_hs[i];
-        amax = fmaxf(amax, v.x);
-        nmax = fmaxf(nmax, v.y);
-        emax = fmaxf(emax, v.z);
-    }
-}
-
 hipError_t launch_qprep(const QprepArgs& a, hipStream_t s) {
     const int r = (a.mode & 2) ? a.r : 0;
     dim3 g1((a.H + 15) / 16, a.B);
@@ -252,15 +241,6 @@ hipError_t launch_qprep(const QprepArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------- the scorer
-
-constexpr int SCORE_TPW = 32;                       // 16-row tiles per wave
-constexpr int SCORE_ROWS_PER_BLOCK = 4 * 16 * SCORE_TPW;
-
-__device__ __forceinline__ float wave_max16(float m) {
-    m = fmaxf(m, __shfl_xor(m, 16));
-    m = fmaxf(m, __shfl_xor(m, 32));
-    return m;
-}
 
 // __shfl_xor whose lane arithmetic the compiler cannot share between call
 // sites: shared lane addresses would stay live across the scan loops and
@@ -296,29 +276,12 @@ __device__ __forceinline__ float row_sq(const bf16x8_t (&xf)[KS]) {
     return s2;
 }
 
-// Epilogue of one 16-row tile for the lane holding row `row`: key~ (max over
-// heads, already reduced) and the lane's partial of ||x||^2.  The scorer
-// keeps the per-sequence extremes of key~ and of ||x||^2; the selection
-// derives the certified band of every key from them.
+// Per-lane extremes of a wave's rows: the scorer keeps the per-sequence extremes
+// of key~ and of ||x||^2; the selection derives the certified band of every key
+// from them.
 struct TileOut {
     float kmax, kmin, nu2m, bmm;
 };
-
-__device__ __forceinline__ void tile_epilogue(const ScoreArgs& a, int b, int g, int64_t row, bool valid, float m,
-                                              float s2, TileOut& t) {
-    s2 += __shfl_xor(s2, 16);
-    s2 += __shfl_xor(s2, 32);
-    if (valid) {
-        t.nu2m = fmaxf(t.nu2m, s2);
-        t.kmax = fmaxf(t.kmax, m);
-        t.kmin = fminf(t.kmin, m);
-        if (g == 0) {
-            const int64_t o = (int64_t)b * a.A + row;
-            a.kt[o] = m;
-            if (a.key) a.key[o] = m;
-        }
-    }
-}
 
 __device__ __forceinline__ void score_finish(const ScoreArgs& a, int b, int lane, TileOut t, bool ub) {
     t.nu2m = wave_max_all(t.nu2m);
@@ -332,85 +295,6 @@ __device__ __forceinline__ void score_finish(const ScoreArgs& a, int b, int lane
         atomicMax(sq + SQ_KMAX, key_to_ord(t.kmax));
         if (ub) atomicMax(sq + SQ_BMAX, __float_as_uint(t.bmm));
     }
-}
-
-// Any head count / width within the limits: heads and dims in runtime loops,
-// query fragments re-read from the (cache-resident) qt buffer per tile.
-template <bool UB>
-__global__ __launch_bounds__(256, 2) void score_generic_kernel(ScoreArgs a) {
-    constexpr int KSMAX = D_ROW / 32;
-    __shared__ float4 s_hs[UB ? 128 : 1];
-    __shared__ float s_thr[UB ? 128 : 1];   // -s*_h (trigger margins) or 0
-    const int b = blockIdx.y;
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, g = lane >> 4, c = lane & 15;
-    const int KS = a.n / 32;
-    const int HT = (a.H + 15) / 16;
-    if (UB) {
-        for (int h = tid; h < 16 * HT; h += 256) {
-            const float4 v = reinterpret_cast<const float4*>(a.hsc)[(int64_t)b * a.H + (h % a.H)];
-            s_hs[h] = make_float4(scaled_a(a.cert_mult, v.x), v.y, v.z, v.w);
-            s_thr[h] = a.thr ? -(float)a.thr[(int64_t)b * a.H + (h % a.H)] : 0.f;
-        }
-        __syncthreads();
-    }
-    if (blockIdx.x == 0 && threadIdx.x < 64) store_head_maxima(a, b, threadIdx.x);
-    const int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * (16 * SCORE_TPW);
-    if (r0 >= a.A) return;
-    const int64_t rend = min(a.A, r0 + (int64_t)(16 * SCORE_TPW));
-    const int64_t rlast = rend - 1;
-    const uint16_t* qtb = a.qt + (int64_t)b * a.H * a.n;
-    const uint16_t* xb = a.x + (int64_t)b * a.xbs;
-    float amax = 0.f, nmax = 0.f, emax = 0.f, tabs = 0.f;
-    if (UB) {
-        staged_head_maxima(s_hs, 16 * HT, amax, nmax, emax);
-        for (int i = 0; i < 16 * HT; ++i) tabs = fmaxf(tabs, fabsf(s_thr[i]));
-    }
-    TileOut to{-INFINITY, INFINITY, 0.f, 0.f};
-    for (int64_t t0 = r0; t0 < rend; t0 += 16) {
-        const int64_t row = t0 + c;
-        const bool valid = row < rend;
-        const int64_t lrow = min(row, rlast);
-        bf16x8_t xf[KSMAX];
-#pragma unroll
-        for (int ks = 0; ks < KSMAX; ++ks)
-            xf[ks] = (ks < KS) ? *reinterpret_cast<const bf16x8_t*>(xb + lrow * a.xs + 32 * ks + 8 * g) : bf16x8_t{};
-        float et = 0.f, ep = 0.f, ga = 0.f;
-        if (UB) {
-            const int64_t o = (int64_t)b * a.T + lrow;
-            et = a.eta[o];
-            ep = a.eps[o];
-            ga = a.gam[o];
-        }
-        float m = -INFINITY, ubv = -INFINITY;
-        for (int ht = 0; ht < HT; ++ht) {
-            const int hq = (16 * ht + c) % a.H;
-            f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KSMAX; ++ks) {
-                if (ks < KS) {
-                    const bf16x8_t q = *reinterpret_cast<const bf16x8_t*>(qtb + (int64_t)hq * a.n + 32 * ks + 8 * g);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q, xf[ks], acc, 0, 0, 0);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                m = fmaxf(m, acc[i]);
-                if (UB) {
-                    const float4 hs = s_hs[16 * ht + 4 * g + i];
-                    ubv = fmaxf(ubv, (acc[i] + fmaf(hs.x, et, fmaf(hs.y, ep, hs.z * ga))) + s_thr[16 * ht + 4 * g + i]);
-                }
-            }
-        }
-        m = wave_max16(m);
-        tile_epilogue(a, b, g, row, valid, m, row_sq<KSMAX>(xf), to);
-        if (UB) {
-            ubv = wave_max16(ubv);
-            if (valid) to.bmm = fmaxf(to.bmm, fmaf(amax, et, fmaf(nmax, ep, emax * ga)) + tabs);
-            if (g == 0 && valid) a.ub[(int64_t)b * a.A + row] = ubv;
-        }
-    }
-    score_finish(a, b, lane, to, UB);
 }
 
 // ------------------------------------------------------ streaming scorer
@@ -536,15 +420,26 @@ __device__ __forceinline__ void put4(float& v0, float& v1, float& v2, float& v3,
     v3 = (i == 3) ? x : v3;
 }
 
-template <int HT, int KS, bool UB>
-__global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int tpw) {
+// SPLIT: heads x width do not fit one wave's registers (HT KS > 32), so `parts`
+// waves of the block share every tile, each with 16 HT of the heads and a ring
+// of its own (the second copy of a tile comes from the caches); the partial
+// maxima meet in LDS after the last tile.  4 x 65536 rows of 256 dims, 128 heads:
+// 53 us, 2.5 TB/s of index rows (322 us with the query fragments re-read from L2
+// for every tile); two reads per row and the run-time tile loop bound it.
+// (from 320 dims on the rings leave room for one block per CU, whose waves then
+// have twice the registers)
+template <int HT, int KS, bool UB, bool SPLIT>
+__global__ __launch_bounds__(256, KS >= 10 ? 1 : 2) void score_stream_kernel(ScoreArgs a, int tpw, int nparts) {
     using Gm = StreamGeom<KS, UB>;
     constexpr int N8 = Gm::N8, STAGE = Gm::STAGE, NST = Gm::NST, RUN = Gm::RUN, LPT = Gm::LPT;
-    constexpr int TST = STREAM_WAVES;   // block tiles between consecutive tiles of a wave
+    constexpr int NT = SPLIT ? 0 : 2;               // cache policy of the tile loads: nt where a tile is read once
+    const int parts = SPLIT ? nparts : 1;
+    const int TST = STREAM_WAVES / parts;           // block tiles between consecutive tiles of a wave
     extern __shared__ __align__(16) uint8_t smem[];
     const int b = blockIdx.y;
     const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tl = SPLIT ? wave / parts : wave, hp = SPLIT ? wave % parts : 0;   // tile lane, part of the heads
     uint8_t* wbase = smem + wave * Gm::WAVE;
     uint8_t* rvbase = wbase + NST * STAGE;                                   // [NST][64] row scalars
     float* s_key = reinterpret_cast<float*>(wbase + NST * (STAGE + Gm::RV));   // [64 q + lane]
@@ -553,9 +448,9 @@ __global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int t
     float* s_ub = keys ? s_key + 16 * Gm::KT / 2 : s_key;
     // block span [bs0, bs1); this wave's tile j covers rows r0 + 16 TST j + [0, 16)
     if (blockIdx.x == 0 && threadIdx.x < 64) store_head_maxima(a, b, threadIdx.x);
-    const int64_t bs0 = (int64_t)blockIdx.x * STREAM_WAVES * 16 * tpw;
+    const int64_t bs0 = (int64_t)blockIdx.x * TST * 16 * tpw;
     if (bs0 >= a.A) return;
-    const int64_t bs1 = min(a.A, bs0 + (int64_t)STREAM_WAVES * 16 * tpw);
+    const int64_t bs1 = min(a.A, bs0 + (int64_t)TST * 16 * tpw);
     const int64_t nbt = (bs1 - bs0 + 15) / 16;
 
     // the sequence's query rows qt[b] (H x N bf16), staged once per block in
@@ -565,7 +460,7 @@ __global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int t
     bf16x8_t qf[HT][KS];
     {
         constexpr int QROW = 2 * Gm::N + 16;
-        static_assert(16 * HT * QROW <= STREAM_WAVES * Gm::WAVE, "query rows fit the block's LDS");
+        static_assert((SPLIT ? 128 : 16 * HT) * QROW <= STREAM_WAVES * Gm::WAVE, "query rows fit the block's LDS");
         const uint16_t* qtb = a.qt + (int64_t)b * a.H * a.n;
         for (int p = threadIdx.x; p < a.H * N8; p += 64 * STREAM_WAVES) {
             const int h = p / N8, j = p % N8;
@@ -575,16 +470,19 @@ __global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int t
         __syncthreads();
 #pragma unroll
         for (int ht = 0; ht < HT; ++ht) {
-            const int h = (16 * ht + c) % a.H;
+            const int h = (16 * (HT * hp + ht) + c) % a.H;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
                 qf[ht][ks] = *reinterpret_cast<const bf16x8_t*>(smem + h * QROW + 64 * ks + 16 * g);
         }
         __syncthreads();   // read out before the rings overwrite it
     }
-    if (wave >= nbt) return;
-    const int ntl = (int)((nbt - 1 - wave) / TST + 1);
-    const int64_t r0 = bs0 + 16 * wave;
+    if (tl >= nbt) {
+        if (SPLIT) __syncthreads();   // (the one of the waves with tiles)
+        return;
+    }
+    const int ntl = (int)((nbt - 1 - tl) / TST + 1);
+    const int64_t r0 = bs0 + 16 * tl;
 
     // (UB) A operand of the bound step: scalar g of head slot 16 ht + c (for
     // g = 3: -s*_h or zero), and in lane 16 g + c the maximum over heads of
@@ -592,16 +490,18 @@ __global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int t
     float hsf[UB ? HT : 1];
     float coef = 0.f;
 
-    const uint32_t rowb = (uint32_t)(a.xs * 2);   // row stride in bytes
+    // byte offsets inside a tile (64-bit where any row stride must do)
+    using off_t = typename std::conditional<SPLIT, uint64_t, uint32_t>::type;
+    const off_t rowb = (off_t)(a.xs * 2);   // row stride in bytes
     const uint8_t* span = reinterpret_cast<const uint8_t*>(a.x + (int64_t)b * a.xbs + r0 * a.xs);
-    uint32_t voff[KS];
+    off_t voff[KS];
     int vrow[KS];
 #pragma unroll
     for (int j = 0; j < KS; ++j) {
         const int q = 64 * j + lane;
         const int R = q / N8, S = q % N8;
         vrow[j] = R;
-        voff[j] = (uint32_t)R * rowb + 16u * (uint32_t)((S + R) % N8);
+        voff[j] = (off_t)R * rowb + 16u * (uint32_t)((S + R) % N8);
     }
     // (UB) source of this lane's row scalar: scalar g of row c of tile 0
     const float* rvsrc = nullptr;
@@ -623,10 +523,10 @@ __global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int t
         const int nv = (int)min((int64_t)16, bs1 - (r0 + (int64_t)(TST * 16) * t));   // rows of this tile
 #pragma unroll
         for (int j = 0; j < KS; ++j) {
-            uint32_t o = voff[j];
-            if (nv < 16 && vrow[j] >= nv) o -= (uint32_t)(vrow[j] - (nv - 1)) * rowb;
+            off_t o = voff[j];
+            if (nv < 16 && vrow[j] >= nv) o -= (off_t)(vrow[j] - (nv - 1)) * rowb;
             __builtin_amdgcn_global_load_lds((gbl_void_t*)(tb + o), (lds_void_t*)(wbase + stage * STAGE + 1024 * j),
-                                             16, 0, 2 /* nt */);
+                                             16, 0, NT);
         }
         issue_rv(t, stage, nv);
     };
@@ -636,7 +536,7 @@ __global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int t
 #pragma unroll
         for (int j = 0; j < KS; ++j)
             __builtin_amdgcn_global_load_lds((gbl_void_t*)(tb + voff[j]),
-                                             (lds_void_t*)(wbase + stage * STAGE + 1024 * j), 16, 0, 2 /* nt */);
+                                             (lds_void_t*)(wbase + stage * STAGE + 1024 * j), 16, 0, NT);
         issue_rv(t, stage, 16);
     };
     // operand fragments (and the row scalar) of the tile in `stage`
@@ -676,7 +576,7 @@ __global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int t
     if (UB) {
 #pragma unroll
         for (int ht = 0; ht < HT; ++ht) {
-            const int h = (16 * ht + c) % a.H;
+            const int h = (16 * (HT * hp + ht) + c) % a.H;
             // slot g = 3: -s*_h against a row scalar of 1 (trigger margins), else 0
             const float v = g < 3 ? a.hsc[((int64_t)b * a.H + h) * 4 + g]
                                   : (a.thr ? -(float)a.thr[(int64_t)b * a.H + h] : 0.f);
@@ -694,8 +594,10 @@ __global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int t
     auto group_out = [&](int q, float m, float s2, float u) {
         if (group_row(q) < bs1) {
             to.nu2m = fmaxf(to.nu2m, s2);
-            to.kmax = fmaxf(to.kmax, m);
-            to.kmin = fminf(to.kmin, m);
+            if (!SPLIT || !keys) {   // (with parts, of the combined maxima below)
+                to.kmax = fmaxf(to.kmax, m);
+                to.kmin = fminf(to.kmin, m);
+            }
         }
         if (keys) s_key[64 * q + lane] = m;
         if (UB) s_ub[64 * q + lane] = u;
@@ -794,15 +696,28 @@ __global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int t
     float* kto = a.kt + (int64_t)b * a.A;
     float* kuo = a.key ? a.key + (int64_t)b * a.A : nullptr;
     float* ubo = UB ? a.ub + (int64_t)b * a.A : nullptr;
-    for (int q = 0; q < (ntl + 3) / 4; ++q) {
+    if (SPLIT) __syncthreads();   // the parts' maxima are in LDS; each part finishes its share of the groups
+    for (int q = hp; q < (ntl + 3) / 4; q += parts) {
         const int64_t row = group_row(q);
         if (row < bs1) {
+            float m = keys ? s_key[64 * q + lane] : 0.f, u = UB ? s_ub[64 * q + lane] : 0.f;
+            if constexpr (SPLIT) {
+                constexpr int W4 = Gm::WAVE / 4;
+                for (int o = 1; o < parts; ++o) {
+                    const int d = ((hp + o) % parts - hp) * W4;   // another part's buffers, in floats
+                    if (keys) m = fmaxf(m, s_key[64 * q + lane + d]);
+                    if (UB) u = fmaxf(u, s_ub[64 * q + lane + d]);
+                }
+                if (keys) {
+                    to.kmax = fmaxf(to.kmax, m);
+                    to.kmin = fminf(to.kmin, m);
+                }
+            }
             if (keys) {
-                const float m = s_key[64 * q + lane];
                 kto[row] = m;
                 if (kuo) kuo[row] = m;
             }
-            if (UB) ubo[row] = s_ub[64 * q + lane];
+            if (UB) ubo[row] = u;
         }
     }
     if (UB) {
@@ -817,46 +732,75 @@ __global__ __launch_bounds__(256, 2) void score_stream_kernel(ScoreArgs a, int t
 
 // tiles per wave: enough waves for two blocks per CU, spans of 8..tmax tiles
 // (tmax: the tiles whose keys, or keys and bounds, the wave's LDS buffer holds)
-static int stream_tpw(const ScoreArgs& a, int tmax) {
+static int stream_tpw(const ScoreArgs& a, int tmax, int parts) {
     const int64_t tiles = (int64_t)a.B * ((a.A + 15) / 16);
-    const int64_t waves = 2LL * 256 * STREAM_WAVES;
+    const int64_t waves = 2LL * 256 * STREAM_WAVES / parts;
     int64_t tpw = (tiles + waves - 1) / waves;
     tpw = tpw < 8 ? 8 : (tpw > tmax ? tmax : tpw);
     return (int)tpw;
 }
 
-template <int HT, int KS, bool UB>
-static void launch_stream(const ScoreArgs& a, hipStream_t s) {
+template <int HT, int KS, bool UB, bool SPLIT>
+static void launch_stream(const ScoreArgs& a, int parts, hipStream_t s) {
     // without keys the bounds take the whole key buffer (twice the tiles per wave)
-    const int tpw = stream_tpw(a, (UB && a.no_keys) ? StreamGeom<KS, UB>::KT : StreamGeom<KS, UB>::TPW_MAX);
-    const int64_t rows_per_block = (int64_t)STREAM_WAVES * 16 * tpw;   // block span
+    const int tpw = stream_tpw(a, (UB && a.no_keys) ? StreamGeom<KS, UB>::KT : StreamGeom<KS, UB>::TPW_MAX, parts);
+    const int64_t rows_per_block = (int64_t)(STREAM_WAVES / parts) * 16 * tpw;   // block span
     dim3 grid((unsigned)((a.A + rows_per_block - 1) / rows_per_block), a.B);
     const size_t sm = STREAM_WAVES * (size_t)StreamGeom<KS, UB>::WAVE;
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_stream_kernel<HT, KS, UB>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&score_stream_kernel<HT, KS, UB, SPLIT>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-    hipLaunchKernelGGL((score_stream_kernel<HT, KS, UB>), grid, dim3(256), sm, s, a, tpw);
+    hipLaunchKernelGGL((score_stream_kernel<HT, KS, UB, SPLIT>), grid, dim3(256), sm, s, a, tpw, parts);
 }
 
-template <int HT, int KS>
-static void launch_fast(const ScoreArgs& a, hipStream_t s) {
+template <int HT, int KS, bool SPLIT = false>
+static void launch_fast(const ScoreArgs& a, hipStream_t s, int parts = 1) {
     if (a.ub)
-        launch_stream<HT, KS, true>(a, s);
+        launch_stream<HT, KS, true, SPLIT>(a, parts, s);
     else
-        launch_stream<HT, KS, false>(a, s);
+        launch_stream<HT, KS, false, SPLIT>(a, parts, s);
 }
 
+// HT KS <= 32 query fragments per wave: 128 registers, two blocks per CU
 template <int HT>
-static bool dispatch_ks(const ScoreArgs& a, hipStream_t s, int KS) {
+static void dispatch_ks(const ScoreArgs& a, hipStream_t s, int KS) {
     switch (KS) {
-        case 1: launch_fast<HT, 1>(a, s); return true;
-        case 2: launch_fast<HT, 2>(a, s); return true;
-        case 3: launch_fast<HT, 3>(a, s); return true;
-        case 4: launch_fast<HT, 4>(a, s); return true;
-        case 5: if (HT <= 4) { launch_fast<(HT <= 4 ? HT : 4), 5>(a, s); return true; } return false;
-        case 6: if (HT <= 4) { launch_fast<(HT <= 4 ? HT : 4), 6>(a, s); return true; } return false;
-        case 7: if (HT <= 4) { launch_fast<(HT <= 4 ? HT : 4), 7>(a, s); return true; } return false;
-        case 8: if (HT <= 4) { launch_fast<(HT <= 4 ? HT : 4), 8>(a, s); return true; } return false;
-        default: return false;
+        case 1: launch_fast<HT, 1>(a, s); return;
+        case 2: launch_fast<HT, 2>(a, s); return;
+        case 3: launch_fast<HT, 3>(a, s); return;
+        case 4: launch_fast<HT, 4>(a, s); return;
+        default: break;
+    }
+    if constexpr (HT <= 4) {
+        switch (KS) {
+            case 5: launch_fast<HT, 5>(a, s); return;
+            case 6: launch_fast<HT, 6>(a, s); return;
+            case 7: launch_fast<HT, 7>(a, s); return;
+            default: launch_fast<HT, 8>(a, s); return;
+        }
+    } else {   // 65 to 128 heads: two parts of 64
+        switch (KS) {
+            case 5: launch_fast<4, 5, true>(a, s, 2); return;
+            case 6: launch_fast<4, 6, true>(a, s, 2); return;
+            case 7: launch_fast<4, 7, true>(a, s, 2); return;
+            default: launch_fast<4, 8, true>(a, s, 2); return;
+        }
+    }
+}
+
+// rows of 288 to 576 dims: parts of 32 heads (at most 36 fragments per wave)
+static void dispatch_wide(const ScoreArgs& a, hipStream_t s, int KS) {
+    const int parts = a.H <= 32 ? 1 : (a.H <= 64 ? 2 : 4);
+    switch (KS) {
+        case 9: launch_fast<2, 9, true>(a, s, parts); return;
+        case 10: launch_fast<2, 10, true>(a, s, parts); return;
+        case 11: launch_fast<2, 11, true>(a, s, parts); return;
+        case 12: launch_fast<2, 12, true>(a, s, parts); return;
+        case 13: launch_fast<2, 13, true>(a, s, parts); return;
+        case 14: launch_fast<2, 14, true>(a, s, parts); return;
+        case 15: launch_fast<2, 15, true>(a, s, parts); return;
+        case 16: launch_fast<2, 16, true>(a, s, parts); return;
+        case 17: launch_fast<2, 17, true>(a, s, parts); return;
+        default: launch_fast<2, 18, true>(a, s, parts); return;
     }
 }
 
@@ -864,18 +808,11 @@ hipError_t launch_score(const ScoreArgs& a, hipStream_t s) {
     if (a.A <= 0) return hipSuccess;
     const int KS = a.n / 32;
     const int HT = (a.H + 15) / 16;
-    bool done = false;
-    if (HT == 1) done = dispatch_ks<1>(a, s, KS);
-    else if (HT == 2) done = dispatch_ks<2>(a, s, KS);
-    else if (HT <= 4) done = dispatch_ks<4>(a, s, KS);
-    else if (HT <= 8) done = dispatch_ks<8>(a, s, KS);
-    if (!done) {
-        dim3 grid((unsigned)((a.A + SCORE_ROWS_PER_BLOCK - 1) / SCORE_ROWS_PER_BLOCK), a.B);
-        if (a.ub)
-            hipLaunchKernelGGL((score_generic_kernel<true>), grid, dim3(256), 0, s, a);
-        else
-            hipLaunchKernelGGL((score_generic_kernel<false>), grid, dim3(256), 0, s, a);
-    }
+    if (KS > 8) dispatch_wide(a, s, KS);
+    else if (HT == 1) dispatch_ks<1>(a, s, KS);
+    else if (HT == 2) dispatch_ks<2>(a, s, KS);
+    else if (HT <= 4) dispatch_ks<4>(a, s, KS);
+    else dispatch_ks<8>(a, s, KS);
     return hipGetLastError();
 }
 
