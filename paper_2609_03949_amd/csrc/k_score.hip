@@ -696,28 +696,37 @@ __global__ __launch_bounds__(256, KS >= 10 ? 1 : 2) void score_stream_kernel(Sco
     float* kto = a.kt + (int64_t)b * a.A;
     float* kuo = a.key ? a.key + (int64_t)b * a.A : nullptr;
     float* ubo = UB ? a.ub + (int64_t)b * a.A : nullptr;
-    if (SPLIT) __syncthreads();   // the parts' maxima are in LDS; each part finishes its share of the groups
-    for (int q = hp; q < (ntl + 3) / 4; q += parts) {
-        const int64_t row = group_row(q);
-        if (row < bs1) {
-            float m = keys ? s_key[64 * q + lane] : 0.f, u = UB ? s_ub[64 * q + lane] : 0.f;
-            if constexpr (SPLIT) {
-                constexpr int W4 = Gm::WAVE / 4;
-                for (int o = 1; o < parts; ++o) {
-                    const int d = ((hp + o) % parts - hp) * W4;   // another part's buffers, in floats
-                    if (keys) m = fmaxf(m, s_key[64 * q + lane + d]);
-                    if (UB) u = fmaxf(u, s_ub[64 * q + lane + d]);
-                }
-                if (keys) {
-                    to.kmax = fmaxf(to.kmax, m);
-                    to.kmin = fminf(to.kmin, m);
-                }
+    if constexpr (SPLIT) {
+        __syncthreads();   // the parts' maxima are in LDS; each part finishes its share of the groups
+        constexpr int W4 = Gm::WAVE / 4;
+        for (int q = hp; q < (ntl + 3) / 4; q += parts) {
+            const int64_t row = group_row(q);
+            if (row >= bs1) continue;
+            float m = -INFINITY, u = -INFINITY;
+            for (int o = 0; o < parts; ++o) {
+                const int d = (o - hp) * W4;   // part o's buffers, in floats
+                if (keys) m = fmaxf(m, s_key[64 * q + lane + d]);
+                if (UB) u = fmaxf(u, s_ub[64 * q + lane + d]);
             }
             if (keys) {
+                to.kmax = fmaxf(to.kmax, m);
+                to.kmin = fminf(to.kmin, m);
                 kto[row] = m;
                 if (kuo) kuo[row] = m;
             }
             if (UB) ubo[row] = u;
+        }
+    } else {
+        for (int q = 0; q < (ntl + 3) / 4; ++q) {
+            const int64_t row = group_row(q);
+            if (row < bs1) {
+                if (keys) {
+                    const float m = s_key[64 * q + lane];
+                    kto[row] = m;
+                    if (kuo) kuo[row] = m;
+                }
+                if (UB) ubo[row] = s_ub[64 * q + lane];
+            }
         }
     }
     if (UB) {
