@@ -370,7 +370,7 @@ struct ExLds {
     bool qlds;
 };
 
-__device__ __forceinline__ ExLds ex_carve(uint8_t* lds, int H, int n) {
+__device__ __forceinline__ ExLds ex_carve(uint8_t* lds, int H, int n, int bytes = RES_LDS) {
     ExLds e;
     size_t o = 0;
     e.qlds = H * n <= EX_QT_MAX;
@@ -386,7 +386,7 @@ __device__ __forceinline__ ExLds ex_carve(uint8_t* lds, int H, int n) {
     e.list = reinterpret_cast<uint32_t*>(lds + o);
     o += RES_WAVES * 64 * 4;
     e.x = reinterpret_cast<uint16_t*>(lds + o);
-    const int avail = (int)(((size_t)RES_LDS - o) / ((size_t)32 * n));   // 16 rows of n bf16 per wave
+    const int avail = (int)(((size_t)bytes - o) / ((size_t)32 * n));   // 16 rows of n bf16 per wave
     e.nwx = avail < RES_WAVES ? avail : RES_WAVES;
     return e;
 }
@@ -583,14 +583,14 @@ __device__ __forceinline__ void exact_keys_block(const SelectArgs& a, int b, int
 
 
 // Rank of the undecided rows by (exact key desc, index asc): the first
-// `need` of them get flag 1; returns (in thread 0's view, via *theta_ord) the
+// `need` of them are passed to mark; returns (in thread 0's view, via *theta_ord) the
 // key of the last of them.  Pairwise counting with the list staged in LDS
 // when it is short; otherwise a radix select on the 96-bit composite
 // (order key, ~index), whose larger values come first.
 // ak_lds (optional): the keys already in LDS (the first RANK_QUAD_MAX of them).
-__device__ __forceinline__ void rank_winners(const int32_t* amb, const uint64_t* ak, int64_t namb, int64_t need, uint8_t* fb,
-                             uint32_t* xin, uint8_t* lds, uint64_t* s_theta, uint8_t mark = 1,
-                             const uint64_t* ak_lds = nullptr) {
+template <typename Mark>
+__device__ __forceinline__ void rank_winners(const int32_t* amb, const uint64_t* ak, int64_t namb, int64_t need, Mark mark,
+                                             uint8_t* lds, uint64_t* s_theta, const uint64_t* ak_lds = nullptr) {
     const int tid = threadIdx.x;
     if (namb <= RANK_QUAD_MAX) {
         uint64_t* s_kc = reinterpret_cast<uint64_t*>(lds);
@@ -610,8 +610,7 @@ __device__ __forceinline__ void rank_winners(const int32_t* amb, const uint64_t*
                 rank += (kj > ki) || (kj == ki && s_u[j] < ui);
             }
             if (rank < need) {
-                fb[ui] = mark;
-                atomicAdd(&xin[(int64_t)(ui / CB_KEYS) * BLK_WORDS], 1u);
+                mark(ui);
                 if (rank == need - 1) *s_theta = ki;
             }
         }
@@ -672,8 +671,7 @@ __device__ __forceinline__ void rank_winners(const int32_t* amb, const uint64_t*
         const uint64_t hi = ak[i];
         const uint32_t lo = ~(uint32_t)amb[i];
         if (hi > pre_hi || (hi == pre_hi && lo >= pre_lo)) {
-            fb[amb[i]] = mark;
-            atomicAdd(&xin[(int64_t)(amb[i] / CB_KEYS) * BLK_WORDS], 1u);
+            mark(amb[i]);
         }
     }
     if (tid == 0) *s_theta = pre_hi;
@@ -875,7 +873,11 @@ __global__ __launch_bounds__(RES_THREADS, 1) void sel_resolve_kernel(SelectArgs 
     const int32_t* al = amb_lds ? s_amb : amb;
     const ExLds L = ex_carve(lds, a.H, a.n);
     exact_keys_block<false>(a, b, namb, al, ak, L, next_up_f32(2.0f * E), 0, 1, &qpre, s_ak);
-    rank_winners(al, ak, namb, need2, fb, blkb + BW_XIN, lds, &s_theta, 1, s_ak);
+    auto mark = [&](int32_t u) {
+        fb[u] = 1;
+        atomicAdd(&blkb[(int64_t)(u / CB_KEYS) * BLK_WORDS + BW_XIN], 1u);
+    };
+    rank_winners(al, ak, namb, need2, mark, lds, &s_theta, s_ak);
     if (tid == 0) a.theta[b] = ord_to_f64(s_theta);
 }
 
@@ -937,6 +939,146 @@ __global__ __launch_bounds__(SEL_THREADS) void compact_kernel(CompactArgs a) {
     if (a.total && c == a.nblk - 1 && tid == 0) a.total[b] = (int32_t)(base + tot);
 }
 
+// ------------------------------------------- the whole selection of a short archive
+//
+// Up to SMALL_A rows: one block per sequence holds the keys~ in registers
+// (thread t: rows t + 512 j) and does the whole selection, so there is no
+// bracket to guess, no candidate list, and no launch between the steps: a
+// histogram of the key range (refined where a bin holds many keys) gives
+// [LO, HI] as in the resolve block, the undecided rows get their exact keys and
+// ranks as there, and S is written from 64-row masks in LDS.  Bound by latency:
+// one read of the keys, a few LDS passes and the exact keys' round trips.
+// Measured against the four launches: 8064 rows, 16 heads 18.8 against 30.4 us;
+// 32512 rows, 128 heads 32.7 against 34.4 (8 sequences) and 42.9 against 42.3
+// (16), where one block's passes over its keys have caught up; hence the line.
+constexpr int SMALL_A = 16384;
+constexpr int SMALL_LDS = RES_LDS - SMALL_A / 8;   // dynamic LDS (the masks are static)
+constexpr int SMALL_BIN_MAX = 64;     // keys of the k-th key's bin that need no refinement
+constexpr int SMALL_WORDS = SMALL_A / 64;
+
+template <int PER>
+__global__ __launch_bounds__(RES_THREADS, 1) void sel_small_kernel(SelectArgs a) {
+    extern __shared__ __align__(16) uint8_t lds[];
+    __shared__ uint32_t s_w[RES_WAVES];
+    __shared__ uint32_t s_namb;
+    __shared__ int s_bin;
+    __shared__ uint64_t s_theta;
+    __shared__ int32_t s_amb[AMB_LDS];
+    __shared__ uint64_t s_ak[RANK_QUAD_MAX];
+    __shared__ unsigned long long s_mask[SMALL_WORDS];   // selected rows, 64 per word
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int A = (int)a.A;
+    uint32_t* sq = a.seq + (int64_t)b * SQ_WORDS;
+    uint8_t* fb = a.flags + (int64_t)b * a.fstride;
+    const float* kt = a.kt + (int64_t)b * a.A;
+    int32_t* amb = a.amb + (int64_t)b * a.A;
+    uint64_t* ak = a.ambkey + (int64_t)b * a.A;
+    float k[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) k[j] = kt[min(tid + RES_THREADS * j, A - 1)];
+    float lo = ord_to_key(sq[SQ_KMIN]), hi = ord_to_key(sq[SQ_KMAX]);
+    const float E = key_band_f32(sq, a.n);
+    // the query rows of the exact re-scoring at the end, in flight from here on
+    u16x8_t qpre[EX_QP];
+    qt_prefetch(a, b, qpre);
+    uint32_t* s_h = reinterpret_cast<uint32_t*>(lds);
+    if (tid == 0) {
+        s_namb = 0u;
+        s_theta = f64_to_ord(-INFINITY);
+    }
+    // the bin of the k-th largest key~; [lo, hi] shrinks to it while it holds many
+    float sc = 0.f;
+    int db = 0;
+    for (int round = 0; round < 4; ++round) {
+        sc = bin_scale(lo, hi);
+        for (int i = tid; i < HIST_BINS; i += RES_THREADS) s_h[i] = 0u;
+        if (tid == 0) s_bin = -1;
+        lds_barrier();
+        uint32_t nab = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            if (tid + RES_THREADS * j < A) {
+                nab += k[j] > hi;
+                if (k[j] >= lo && k[j] <= hi) atomicAdd(&s_h[bin_of(k[j], lo, sc)], 1u);
+            }
+        }
+        nab = block_sum<RES_THREADS>(nab, s_w);
+        const int64_t need = a.k - (int64_t)nab;
+        const int d = need >= 1 ? find_rank_bin<HIST_BINS, RES_THREADS>(s_h, (uint32_t)need, s_w) : -1;
+        if (d >= 0) s_bin = d;
+        lds_barrier();
+        db = s_bin < 0 ? 0 : s_bin;
+        const bool many = sc > 0.f && s_h[db] > (uint32_t)SMALL_BIN_MAX && round < 3;
+        lds_barrier();   // the histogram is read out
+        if (!many) break;
+        const float nlo = rd_f32(edge_lo_of(db, lo, sc)), nhi = ru_f32(edge_hi_of(db, lo, hi, sc));
+        if (!(nlo > lo || nhi < hi)) break;   // no narrower in fp32
+        lo = nlo;
+        hi = nhi;
+    }
+    const float HI = band_hi(ru_f32(edge_hi_of(db, lo, hi, sc)), E);
+    const float LO = band_lo(rd_f32(edge_lo_of(db, lo, sc)), E);
+    // classification: selected (w > HI), excluded (v < LO), undecided
+    uint32_t nin = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int u = tid + RES_THREADS * j;
+        const bool in = u < A && band_lo(k[j], E) > HI;
+        const bool und = u < A && !in && !(band_hi(k[j], E) < LO);
+        const uint64_t m = __ballot(in), bal = __ballot(und);
+        if (lane == 0) s_mask[RES_WAVES * j + wave] = m;
+        nin += in;
+        if (bal) {
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&s_namb, (uint32_t)__popcll(bal));
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (und) {
+                const uint32_t pos = base + __popcll(bal & ((1ull << lane) - 1ull));
+                amb[pos] = u;
+                if (pos < AMB_LDS) s_amb[pos] = u;
+            }
+        }
+    }
+    nin = block_sum<RES_THREADS>(nin, s_w);
+    const int64_t namb = s_namb;
+    const int64_t need = a.k - (int64_t)nin;   // >= 1 and <= namb by the band argument
+    if (tid == 0) {
+        sq[SQ_TLO] = __float_as_uint(LO);
+        sq[SQ_THI] = __float_as_uint(HI);
+        sq[SQ_NAMB] = (uint32_t)namb;
+        sq[SQ_NCAND2] = 0u;   // the admission's list starts empty
+    }
+    const bool amb_lds = namb <= AMB_LDS;
+    if (!amb_lds) __threadfence_block();
+    __syncthreads();
+    const int32_t* al = amb_lds ? s_amb : amb;
+    const ExLds L = ex_carve(lds, a.H, a.n, SMALL_LDS);
+    exact_keys_block<false>(a, b, namb, al, ak, L, next_up_f32(2.0f * E), 0, 1, &qpre, s_ak);
+    auto mark = [&](int32_t u) { atomicOr(&s_mask[u >> 6], 1ull << (u & 63)); };
+    rank_winners(al, ak, namb, need, mark, lds, &s_theta, s_ak);
+    if (tid == 0) a.theta[b] = ord_to_f64(s_theta);
+    __syncthreads();
+    // word tid: its rows ascending, and their flags for the admission and the trigger
+    const uint64_t w = tid < (A + 63) / 64 ? (uint64_t)s_mask[tid] : 0ull;
+    uint32_t tot;
+    int64_t pos = block_excl_scan<RES_THREADS>((uint32_t)__popcll(w), s_w, tot);
+    int32_t* out = a.sel + (int64_t)b * a.k;
+    for (uint64_t bits = w; bits; bits &= bits - 1)
+        if (pos < a.k) out[pos++] = 64 * tid + __ffsll((unsigned long long)bits) - 1;
+    if (tid < (A + 63) / 64) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            u32x4_t f;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t nib = (uint32_t)(w >> (16 * q + 4 * d)) & 15u;
+                f[d] = (nib & 1u) | ((nib & 2u) << 7) | ((nib & 4u) << 14) | ((nib & 8u) << 21);
+            }
+            *reinterpret_cast<u32x4_t*>(fb + 64 * tid + 16 * q) = f;
+        }
+    }
+}
+
 static hipError_t run_compact(const SelectArgs& s, const uint8_t* flags, uint32_t target, int32_t* out, int64_t stride,
                               int64_t cap, int32_t* total, hipStream_t st) {
     const CompactArgs c{flags, s.fstride, s.blk, s.nblk, s.A, target, out, stride, cap, total};
@@ -962,6 +1104,13 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
         if (a.A == 0) return hipSuccess;
         hipLaunchKernelGGL(fill_u8_kernel, dim3(256), dim3(SEL_THREADS), 0, s, a.flags, (int64_t)a.B * a.fstride,
                            (uint8_t)0);
+        return hipGetLastError();
+    }
+    if (a.A <= SMALL_A) {
+        auto small = a.A <= SMALL_A / 2 ? sel_small_kernel<SMALL_A / 2 / RES_THREADS> : sel_small_kernel<SMALL_A / RES_THREADS>;
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(small), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  SMALL_LDS);
+        hipLaunchKernelGGL(small, dim3(a.B), dim3(RES_THREADS), SMALL_LDS, s, a);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(sel_bracket_kernel, dim3(a.B), dim3(SEL_THREADS), 0, s, a);
@@ -1225,7 +1374,11 @@ __global__ __launch_bounds__(RES_THREADS, 1) void trig_fire_kernel(SelectArgs a)
     }
     if (a.topj > 0 && (int64_t)nf > a.topj) {
         // the top j margins among the candidates are all fired (margin > 0 >= the rest)
-        rank_winners(cl, ak, namb, a.topj, f2, xin, lds, &s_theta, 6);
+        auto mark = [&](int32_t u) {
+            f2[u] = 6;
+            atomicAdd(&xin[(int64_t)(u / CB_KEYS) * BLK_WORDS], 1u);
+        };
+        rank_winners(cl, ak, namb, a.topj, mark, lds, &s_theta);
     } else {
         for (int64_t i = tid; i < namb; i += RES_THREADS)
             if (ak[i] > zero) {
