@@ -442,11 +442,22 @@ int vkv_digest_build(vkv_ctx* ctx, const uint16_t* cache, int64_t B, int64_t T, 
         // Gershgorin: ||P||_2^2 = lambda_max(P P^T) <= max_j sum_k |(P P^T)_jk|.  A row
         // passes if its sum was computed exactly and is <= 1, or if it is <= 1 - 2^-30
         // (a margin far above the fp64 rounding of the sum).
-        HIP_TRY(ctx, launch_gram_rows(P, r, ctx->gram, s));
+        // Sums in any order differ from these by less than 2^-33 where a row passes
+        // (r times 512 products of sum at most 1, 2^-53 each, both ways), so rows
+        // of the quick sums below 1 - 2^-30 - 2^-33 pass; only where one does not
+        // are the sequential sums and their exactness flags formed.
         std::vector<double> rows((size_t)1024);
-        HIP_TRY(ctx, hipMemcpyAsync(rows.data(), ctx->gram, 1024 * 8, hipMemcpyDeviceToHost, s));
+        HIP_TRY(ctx, launch_gram_fast(P, r, ctx->gram, s));
+        HIP_TRY(ctx, hipMemcpyAsync(rows.data(), ctx->gram, (size_t)r * 8, hipMemcpyDeviceToHost, s));
         HIP_TRY(ctx, hipStreamSynchronize(s));
-        for (int j = 0; j < r; ++j) {
+        bool inside = true;
+        for (int j = 0; j < r; ++j) inside = inside && rows[(size_t)j] <= 1.0 - 0x1p-30 - 0x1p-33;
+        if (!inside) {
+            HIP_TRY(ctx, launch_gram_rows(P, r, ctx->gram, s));
+            HIP_TRY(ctx, hipMemcpyAsync(rows.data(), ctx->gram, 1024 * 8, hipMemcpyDeviceToHost, s));
+            HIP_TRY(ctx, hipStreamSynchronize(s));
+        }
+        for (int j = 0; !inside && j < r; ++j) {
             const double g = rows[(size_t)j];
             const bool exact = rows[(size_t)(512 + j)] == 0.0;
             if (!((exact && g <= 1.0) || g <= 1.0 - 0x1p-30))

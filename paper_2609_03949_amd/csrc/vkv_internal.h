@@ -296,6 +296,7 @@ struct AttendArgs {
 hipError_t launch_qprep(const QprepArgs& a, hipStream_t s);
 hipError_t launch_score(const ScoreArgs& a, hipStream_t s);
 hipError_t launch_digest(const DigestArgs& a, hipStream_t s);
+hipError_t launch_gram_fast(const uint16_t* P, int r, double* rowsum, hipStream_t s);
 hipError_t launch_gram_rows(const uint16_t* P, int r, double* rowsum, hipStream_t s);
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 hipError_t launch_admit(const SelectArgs& a, hipStream_t s);

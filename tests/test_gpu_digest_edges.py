@@ -52,3 +52,37 @@ def test_index_build_edges(B, T, r, with_rope, cert):
         if cert:
             for s, want in zip(sc, (eta, eps, gam)):
                 assert np.array_equal(s[b * T:(b + 1) * T].cpu().numpy(), np.asarray(want).reshape(-1))
+
+
+@pytest.mark.parametrize("name,r,ok", [("identity", 64, True), ("identity", 512, True), ("above", 64, False),
+                                       ("overlap", 96, False), ("inside", 160, True), ("zero", 32, True),
+                                       ("nan", 64, False)])
+def test_contractivity_verdict(name, r, ok):
+    """Bases on, above and inside the bound: exact row sums of 1 pass (the sequential
+    check), anything above does not, and the quick check alone serves the rest."""
+    P = torch.eye(512, dtype=torch.float64)[:r]
+    if name == "above":
+        P[3, 3] = 1.0078125                       # the next bf16 above 1
+    if name == "overlap":
+        P[1, 0] = 2.0 ** -20                      # row sums 1 + 2^-20 and above
+    if name == "inside":
+        P = P * 0.75
+        P[:, 300] += 2.0 ** -10
+    if name == "zero":
+        P = P * 0
+    if name == "nan":
+        P[5, 7] = float("nan")
+    T = 40
+    cache = torch.randn(1, T, 576, device="cuda").to(torch.bfloat16)
+    index = torch.full((1, T, 64 + r), 3.0, dtype=torch.bfloat16, device="cuda")
+    sc = [torch.full((1, T), -5.0, device="cuda") for _ in range(3)]
+    ctx = vkv.Context(0)
+    if ok:
+        vkv.digest_build(ctx, cache, P.to(torch.bfloat16).cuda(), r, True, index, *sc)
+        torch.cuda.synchronize()
+        assert all(bool((s >= 0).all()) for s in sc)
+    else:
+        with pytest.raises(vkv.VkvError) as e:
+            vkv.digest_build(ctx, cache, P.to(torch.bfloat16).cuda(), r, True, index, *sc)
+        assert e.value.code == -5 and bool((index == 3.0).all()) and all(bool((s == -5.0).all()) for s in sc)
+    ctx.close()
