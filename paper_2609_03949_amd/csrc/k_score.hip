@@ -27,90 +27,138 @@ namespace vkv {
 // same bits as the sequential FMA chain; the GPU tests compare the digest with
 // the fp64 oracle on inputs spread over 2^60, where other summation orders
 // give other bits), so a chain of 128 of them, i ascending, is the fp64
-// definition.  Wave w computes basis tile w
-// (16 heads x 16 basis rows) of the current chunk of 128 basis rows; one more
-// wave runs the Nq chains on the vector unit meanwhile (a chain of 512 fp64
-// steps on its own, so it overlaps the matrix chains instead of lengthening
-// one of them).  The query rows and the chunk of P are staged as bf16 by
-// direct loads into rows padded to QP_ROW bytes, so the operand reads (16
-// rows, one 16-bit element each) fall into distinct banks; they are widened
-// in registers.  The rope half of qt is loaded at the start and written at
-// the end.  Block (0,b) also clears the step state of sequence b.
+// definition.  The basis goes by in chunks of 64 rows, one 16 x 16 tile per wave
+// and SIMD; a fifth wave runs the sequential vector sums beside the matrix
+// chains: Nq (a chain of 512 fp64 steps) during the first chunk, the certificate
+// sums of a chunk (j ascending) during the next one's chains.  The next chunk's
+// rows load into registers while a chunk is multiplied and go to the other half
+// of a two-stage LDS buffer after it.  Query and basis rows are staged as bf16 in
+// rows padded to QP_ROW bytes, so the operand reads (16 rows, one 16-bit element
+// each) fall into distinct banks; they are widened in registers.  The rope half
+// of qt is loaded at the start and written at the end.  Block (0,b) also clears
+// the step state of sequence b.
+// Bound by that latency: 6.5 us per chunk (128 dependent matrix steps and the
+// widening of their operands), and about 9 us of launch, first loads and the last
+// chunk's sums.  Chunks of 128 rows, staged before their chains and with their
+// sums after them, measured 18.9 / 30.0 / 32.1 us at r = 64 (32 x 128 heads), 160
+// (3 x 40) and 192 (4 x 128); this form 17.5 / 28.6 / 30.3.
 constexpr int QP_ROW = 1040;          // LDS bytes per staged row of 512 bf16
-constexpr int QP_CHUNK_ROWS = 128;    // basis rows staged at a time: one 16-row tile per wave
+constexpr int QP_CHUNK_ROWS = 64;     // basis rows staged at a time: one 16-row tile per wave
 constexpr int QP_MAX_WAVES = QP_CHUNK_ROWS / 16;
 constexpr int QP_WSTRIDE = QP_CHUNK_ROWS + 1;   // doubles per head of the staged w values (heads in distinct banks)
+constexpr int QP_DSTRIDE = QP_CHUNK_ROWS + 2;   // bf16 per head of their rounded values
 constexpr int QP_TAIL_BATCH = 16;              // staged values per LDS batch of the tail sums
 
-// waves with a basis tile (0 without a digest); one more wave takes the Nq chains
+// waves with a basis tile (0 without a digest); one more wave takes the vector sums
 __host__ __device__ inline int qp_tile_waves(int r) {
     const int t = r / 16;
     return t < 0 ? 0 : (t > QP_MAX_WAVES ? QP_MAX_WAVES : t);
 }
 
+__device__ __forceinline__ void qp_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(QprepArgs a) {
-    __shared__ __align__(16) uint8_t s_q[16 * QP_ROW];              // the block's 16 query rows, [h][i]
-    __shared__ __align__(16) uint8_t s_p[QP_CHUNK_ROWS * QP_ROW];   // a chunk of P rows, then its w values
-    __shared__ double s_nq[16];
+    __shared__ __align__(16) uint8_t s_q[16 * QP_ROW];                 // the block's 16 query rows, [h][i]
+    __shared__ __align__(16) uint8_t s_p[2][QP_CHUNK_ROWS * QP_ROW];   // two chunks of P rows
+    __shared__ double s_w[16 * QP_WSTRIDE];                            // a chunk's w values
+    __shared__ uint16_t s_d[16 * QP_DSTRIDE];                          // and RNE(w)
     const int b = blockIdx.y, hb0 = 16 * blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nw = blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (blockIdx.x == 0) {
         if (tid < SQ_WORDS) a.seq[b * SQ_WORDS + tid] = (tid == SQ_KMIN) ? 0xFFFFFFFFu : 0u;
     }
     const int r = (a.mode & 2) ? a.r : 0;
     const int off = (a.mode & 1) ? D_ROPE : 0;
-    const int nq_wave = qp_tile_waves(r);
-    // wave 0, lane 4 hl + t: rope pieces t and t + 4 of head hb0 + hl (loaded now, stored at the end)
+    const int ntw = qp_tile_waves(r);
+    const bool sums = wave == ntw;   // the wave of the vector sums
+    // its lane 4 hl + t: rope pieces t and t + 4 of head hb0 + hl (loaded now, stored at the end)
     const int hl = lane >> 2, t = lane & 3;
     const int h = hb0 + hl;
     const bool have = h < a.H;
     const int64_t bhc = (int64_t)b * a.H + (have ? h : 0);
     u16x8_t rope0 = u16x8_t{}, rope1 = u16x8_t{};
-    if (wave == 0 && (a.mode & 1) && have) {
+    if (sums && (a.mode & 1) && have) {
         const u16x8_t* src = reinterpret_cast<const u16x8_t*>(a.q_rope + bhc * D_ROPE);
         rope0 = src[t];
         rope1 = src[t + 4];
     }
-    typedef __attribute__((address_space(3))) void lds_t;
-    typedef __attribute__((address_space(1))) void gbl_t;
-    // query rows: one 1 KB direct load per row; rows past H are zero
-    for (int row = wave; row < 16; row += nw) {
-        const int h = hb0 + row;
-        if (h < a.H)
-            __builtin_amdgcn_global_load_lds((gbl_t*)(a.q_lat + ((int64_t)b * a.H + h) * D_LAT + 8 * lane),
-                                             (lds_t*)(s_q + row * QP_ROW), 16, 0, 0);
-        else
-            *reinterpret_cast<u32x4_t*>(s_q + row * QP_ROW + 16 * lane) = u32x4_t{0u, 0u, 0u, 0u};
+    // basis rows of chunk ch: wave w moves rows 16 w .. 16 w + 15, one 1 KB load each
+    u32x4_t nx[16];
+    auto load_chunk = [&](int ch) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int row = min(QP_CHUNK_ROWS * ch + 16 * wave + e, r - 1);
+            nx[e] = *reinterpret_cast<const u32x4_t*>(a.P + (int64_t)row * D_LAT + 8 * lane);
+        }
+    };
+    auto store_chunk = [&](int ch) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            *reinterpret_cast<u32x4_t*>(s_p[ch & 1] + (16 * wave + e) * QP_ROW + 16 * lane) = nx[e];
+    };
+    if (!sums) {
+        load_chunk(0);
+    } else {
+        // query rows (zero past H)
+        u32x4_t q[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            q[e] = hb0 + e < a.H ? *reinterpret_cast<const u32x4_t*>(a.q_lat + ((int64_t)b * a.H + hb0 + e) * D_LAT + 8 * lane)
+                                 : u32x4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int e = 0; e < 16; ++e) *reinterpret_cast<u32x4_t*>(s_q + e * QP_ROW + 16 * lane) = q[e];
     }
+    if (!sums) store_chunk(0);
+    qp_barrier();
     // operand rows of this lane: A = query row (lane mod 16), B = basis row
     // 16 wave + (lane mod 16) of the chunk; element k = lane / 16 of each step
     const uint16_t* qa = reinterpret_cast<const uint16_t*>(s_q + (lane & 15) * QP_ROW) + (lane >> 4);
-    const uint16_t* pb = reinterpret_cast<const uint16_t*>(s_p + (16 * wave + (lane & 15)) * QP_ROW) + (lane >> 4);
-    const uint16_t* qn = reinterpret_cast<const uint16_t*>(s_q + (lane & 15) * QP_ROW);   // Nq: head lane mod 16
-    double* s_w = reinterpret_cast<double*>(s_p);   // [16][QP_WSTRIDE] w, then RNE(w), once the chunk is used
-    double* s_d = s_w + 16 * QP_WSTRIDE;
+    const int pb_off = (16 * wave + (lane & 15)) * QP_ROW + 2 * (lane >> 4);
     double anq = 0.0;
-    // tail sums of lane 4 hl + t of wave 0, j ascending over all chunks:
+    // tail sums of lane 4 hl + t of the vector wave, j ascending over all chunks:
     // t=1 ||w||^2, t=2 ||qd - w||^2, t=3 ||qd||^2 (t=0 takes Nq at the end)
     double tsum = 0.0;
+    auto tail = [&](int nj) __attribute__((always_inline)) {
+        const double* w = s_w + hl * QP_WSTRIDE;
+        const uint16_t* dq = s_d + hl * QP_DSTRIDE;
+        // the three sums share one loop: x = w, qd - w or qd by lane (qd - 0
+        // is qd exactly), chosen by selects.  The staged values are read in
+        // batches, all reads of a batch in flight before its chain starts.
+        for (int j0 = 0; j0 < nj; j0 += QP_TAIL_BATCH) {   // (nj is a multiple of 16)
+            double wv[QP_TAIL_BATCH], dv[QP_TAIL_BATCH];
+#pragma unroll
+            for (int e = 0; e < QP_TAIL_BATCH; ++e) {
+                wv[e] = w[j0 + e];
+                dv[e] = (double)bf16_to_f32(dq[j0 + e]);
+            }
+#pragma unroll
+            for (int e = 0; e < QP_TAIL_BATCH; ++e) asm volatile("" : "+v"(wv[e]), "+v"(dv[e]));
+#pragma unroll
+            for (int e = 0; e < QP_TAIL_BATCH; ++e) {
+                const double sub = (t == 2) ? wv[e] : 0.0;
+                const double x = (t == 1) ? wv[e] : dv[e] - sub;
+                tsum = fma(x, x, tsum);
+            }
+        }
+    };
     const int nchunk = (r + QP_CHUNK_ROWS - 1) / QP_CHUNK_ROWS;
     for (int ch = 0; ch < (nchunk > 0 ? nchunk : 1); ++ch) {
         const int j0 = ch * QP_CHUNK_ROWS;
         const int nj = min(QP_CHUNK_ROWS, r - j0);   // basis rows of this chunk (<= 0 without a digest)
-        for (int row = wave; row < nj; row += nw)
-            __builtin_amdgcn_global_load_lds((gbl_t*)(a.P + (int64_t)(j0 + row) * D_LAT + 8 * lane),
-                                             (lds_t*)(s_p + row * QP_ROW), 16, 0, 0);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        const bool tile = wave < nq_wave && 16 * wave < nj;
-        const bool nq = ch == 0 && wave == nq_wave;
+        const bool tile = !sums && 16 * wave < nj;
         f64x4_t acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
-        if (tile) {
-            acc = mfma_f64_rowdot512<false>(qa, pb, qn, anq);
-        } else if (nq) {
+        if (!sums) {
+            const bool more = ch + 1 < nchunk;
+            if (more) load_chunk(ch + 1);
+            if (tile) {
+                double none = 0.0;
+                acc = mfma_f64_rowdot512<false>(qa, reinterpret_cast<const uint16_t*>(s_p[ch & 1] + pb_off), qa, none);
+            }
+            if (more) store_chunk(ch + 1);
+        } else if (ch == 0) {
             // Nq of head lane mod 16, i ascending (eight elements per LDS read)
-            const u16x8_t* qv = reinterpret_cast<const u16x8_t*>(qn);
+            const u16x8_t* qv = reinterpret_cast<const u16x8_t*>(s_q + (lane & 15) * QP_ROW);
 #pragma unroll 4
             for (int i8 = 0; i8 < D_LAT / 8; ++i8) {
                 const u16x8_t v = qv[i8];
@@ -120,8 +168,10 @@ __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(
                     anq = fma(x, x, anq);
                 }
             }
+        } else {
+            tail(QP_CHUNK_ROWS);   // of the chunk before
         }
-        __syncthreads();   // the chunk's rows are read out; its LDS takes the w values
+        qp_barrier();   // the tail's reads are done; s_w and s_d take this chunk's values
         if (tile) {
             // acc[i] = w of head 4 i + lane / 16, basis row j0 + 16 wave + lane mod 16
 #pragma unroll
@@ -130,39 +180,14 @@ __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(
                 const double v = acc[i];
                 const uint16_t d = f64_to_bf16_rne(v);
                 s_w[hh * QP_WSTRIDE + jl] = v;
-                s_d[hh * QP_WSTRIDE + jl] = (double)bf16_to_f32(d);
+                s_d[hh * QP_DSTRIDE + jl] = d;
                 if (hb0 + hh < a.H) a.qt[((int64_t)b * a.H + hb0 + hh) * a.n + off + j0 + jl] = d;
             }
         }
-        if (nq && lane < 16) s_nq[lane] = anq;
-        __syncthreads();
-        if (wave == 0 && t > 0 && nj > 0) {
-            const double* w = s_w + hl * QP_WSTRIDE;
-            const double* dq = s_d + hl * QP_WSTRIDE;
-            // the three sums share one loop: x = w, qd - w or qd by lane (qd - 0
-            // is qd exactly), chosen by selects.  The staged values are read in
-            // batches, all reads of a batch in flight before its chain starts.
-            for (int j0 = 0; j0 < nj; j0 += QP_TAIL_BATCH) {
-                double wv[QP_TAIL_BATCH], dv[QP_TAIL_BATCH];
-#pragma unroll
-                for (int e = 0; e < QP_TAIL_BATCH; ++e) {
-                    const int j = min(j0 + e, nj - 1);
-                    wv[e] = w[j];
-                    dv[e] = dq[j];
-                }
-#pragma unroll
-                for (int e = 0; e < QP_TAIL_BATCH; ++e) asm volatile("" : "+v"(wv[e]), "+v"(dv[e]));
-#pragma unroll
-                for (int e = 0; e < QP_TAIL_BATCH; ++e) {
-                    const double sub = (t == 2) ? wv[e] : 0.0;
-                    const double x = (j0 + e >= nj) ? 0.0 : ((t == 1) ? wv[e] : dv[e] - sub);
-                    tsum = fma(x, x, tsum);   // + 0 past the end: tsum >= 0 is unchanged
-                }
-            }
-        }
-        __syncthreads();   // before the next chunk's rows overwrite the w values
+        qp_barrier();   // the next chunk's rows and this one's values are in place
     }
-    if (wave != 0) return;
+    if (!sums) return;
+    if (nchunk > 0) tail(r - (nchunk - 1) * QP_CHUNK_ROWS);
     // certificate scalars of each head (fp32 upper bounds; Lemma (Index
     // certificate) plus the bf16 rounding of the stored sketch; fixed fp64
     // evaluation order, the same as the oracle's):
@@ -184,9 +209,9 @@ __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(
     }
     r2 += __shfl_xor(r2, 1);
     r2 += __shfl_xor(r2, 2);
-    const double acc_t = t == 0 ? s_nq[hl] : tsum;
     const int base = lane & ~3;
-    const double Nq = __shfl(acc_t, base + 0), Nw = __shfl(acc_t, base + 1);
+    const double acc_t = tsum;
+    const double Nq = __shfl(anq, hl), Nw = __shfl(acc_t, base + 1);
     const double Ne = __shfl(acc_t, base + 2), Nd = __shfl(acc_t, base + 3);
     if (t == 0 && have) {
         const double G = CERT_G;
