@@ -1,7 +1,7 @@
 """The exact row maximum where its ranges, row classes and merge can go wrong:
 copies of the best row in one row class (16 positions apart) and across the
 ranges that are scanned in parallel, rows of very different norms, contexts
-around the 32-row tiles and the 256-row ranges, few and many heads.  Bit for bit
+around the 32-row tiles and the shortest ranges, few and many heads.  Bit for bit
 against the fp64 oracle, and the same on every repetition (the ranges of a call
 without scratch meet in the outputs in no fixed order).
 """
