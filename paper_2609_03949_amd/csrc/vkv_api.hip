@@ -103,32 +103,27 @@ static int check_step(vkv_ctx* ctx, const vkv_step* st) {
 // (one fewer per sequence when rows may be admitted); the admitted rows'
 // capacity (cap, a worst case that is mostly unused) gets splits of its own,
 // the capacity spread over as many splits as there are workgroups per
-// sequence but at least rps rows each and at most ATT_MAX_SPLIT_ROWS (2048: at
-// the near-total admission of 16 sequences of 32768 rows one workgroup per CU
-// and 26 partials per head to merge, 214 + 25 us, against 226 + 35 us with 1024
-// rows and 41 partials), taken
+// sequence but at least rps rows each and at most ATT_MAX_SPLIT_ROWS, taken
 // in turn by a bounded number of workgroups.  Splits past a sequence's actual
 // row count do no work and the combine reads only the splits that hold rows,
 // so a large cap costs workspace, not time.
-constexpr int64_t ATT_BASE_MAX_ROWS = 1024;   // rows of a base split
-
-static void attend_split(const vkv_step* st, int64_t k, int64_t cap, int64_t adm_max, int64_t* splits, int64_t* rps,
+static void attend_split(const vkv_step* st, int64_t k, int64_t cap, int64_t* splits, int64_t* rps,
                          int64_t* base_splits, int64_t* rps_adm, int64_t* adm_blocks) {
     const int64_t nfix = k + st->W;
     const int64_t groups = st->B * ((st->H + ATT_HEADS - 1) / ATT_HEADS);
     const int64_t want = std::max<int64_t>(1, (256 + groups - 1) / groups);      // ~1 workgroup per CU
-    auto rows_for = [&](int64_t n, int64_t lo, int64_t parts, int64_t most) {
+    auto rows_for = [&](int64_t n, int64_t lo, int64_t parts) {
         int64_t rows = (n + parts - 1) / parts;
         rows = std::max<int64_t>(rows, lo);
-        rows = std::min<int64_t>(rows, most);
+        rows = std::min<int64_t>(rows, ATT_MAX_SPLIT_ROWS);
         return (rows + ATT_CHUNK - 1) / ATT_CHUNK * ATT_CHUNK;
     };
     // with admitted rows, one of the ~1-per-CU workgroups is left for them, so
     // that a few admitted rows do not start a second round of workgroups
-    const int64_t rows = rows_for(nfix, 128, cap > 0 ? std::max<int64_t>(1, want - 1) : want, ATT_BASE_MAX_ROWS);
+    const int64_t rows = rows_for(nfix, 128, cap > 0 ? std::max<int64_t>(1, want - 1) : want);
     const int64_t nb = std::max<int64_t>(1, (nfix + rows - 1) / rows);
     const int64_t rest = std::max<int64_t>(0, nfix + cap - nb * rows);   // positions past the base splits
-    const int64_t ra = rows_for(cap, rows, want, adm_max);
+    const int64_t ra = rows_for(cap, rows, want);
     const int64_t nadm = (rest + ra - 1) / ra;
     *rps = rows;
     *base_splits = nb;
@@ -167,16 +162,10 @@ static WsLayout layout(const vkv_step* st, int64_t k, int64_t cap) {
     L.ambkey = o; o = up256(o + (size_t)(B * Aw * 8));
     L.rmx = o; o = up256(o + (size_t)(B * H * RM_MAX_SPLIT * 12));
     // everything above is independent of k and cap; the attention partials last
-    // (sized for admitted splits of at most ATT_BASE_MAX_ROWS rows, of which there
-    // are no fewer than of the longer ones used: the size a caller has asked for
-    // does not depend on this choice)
-    int64_t room;
-    attend_split(st, k, cap, ATT_BASE_MAX_ROWS, &room, &L.rows_per_split, &L.base_splits, &L.rows_per_adm, &L.adm_blocks);
-    attend_split(st, k, cap, ATT_MAX_SPLIT_ROWS, &L.splits, &L.rows_per_split, &L.base_splits, &L.rows_per_adm,
-                 &L.adm_blocks);
+    attend_split(st, k, cap, &L.splits, &L.rows_per_split, &L.base_splits, &L.rows_per_adm, &L.adm_blocks);
     const int64_t HG = (H + ATT_HEADS - 1) / ATT_HEADS;   // partials padded to whole head groups
-    L.part_o = o; o = up256(o + (size_t)(B * room * HG * ATT_HEADS * D_LAT * 2));
-    L.part_ml = o; o = up256(o + (size_t)(B * room * H * 2 * 4));
+    L.part_o = o; o = up256(o + (size_t)(B * L.splits * HG * ATT_HEADS * D_LAT * 2));
+    L.part_ml = o; o = up256(o + (size_t)(B * L.splits * H * 2 * 4));
     L.total = o;
     return L;
 }

@@ -153,7 +153,7 @@ enum BlockWord : int { BW_IN = 0, BW_XIN = 1, BW_ABOVE = 2 };
 constexpr int HIST_BINS = 4096;
 constexpr int ATT_CHUNK = 32;      // rows per attention tile
 constexpr int ATT_HEADS = 128;     // heads per attention workgroup (8 waves x 16)
-constexpr int ATT_MAX_SPLIT_ROWS = 2048;   // rows of one split (row list held in LDS)
+constexpr int ATT_MAX_SPLIT_ROWS = 1024;   // rows of one split (row list held in LDS)
 
 struct WsLayout {
     size_t qt, hsc, seq, kt, flags, flags2, blk, cand, candkey, amb, ambkey, rmx, part_o, part_ml, total;
