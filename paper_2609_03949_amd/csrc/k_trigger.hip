@@ -238,7 +238,7 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
         r1[i] = r2[i] = -1;
     }
     // the screen: a score below T[i] cannot reach the maximum (refresh below);
-    // xcap is the largest ||x||^2 of the rows T allows for, xm this lane's
+    // xcap is the largest finite ||x||^2 of the rows T allows for, xm this lane's
     float T[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     float xcap = 0.f, xm = 0.f;
     // band half-width of a score v of slot i, xb >= ||x|| of every row: e >= KE
@@ -320,12 +320,24 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
         const float xs = s_xn[st][rl];
         // In a long range most halves hold no row that can reach any head's
         // bound: a comparison per score and one ballot skip the rest
-        bool maybe = xs > xcap;
+        const float all4 = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+        const bool odd = !(fabsf(all4) + xs < INFINITY);
+        bool maybe = odd || xs > xcap;
 #pragma unroll
         for (int i = 0; i < 4; ++i) maybe |= acc[i] >= T[i];
         if (__ballot(maybe) == 0) return;
         const int32_t u = s_id[sid][rl];
-        xm = fmaxf(xm, xs);
+        if (__ballot(odd) != 0) {
+            // A score that is not finite says nothing, and a row whose ||x||^2 is
+            // past fp32 has no band: they rank first, so that their exact score
+            // decides, and such a row does not widen the bands of the others
+            const bool wild = !(xs < INFINITY);
+            xm = wild ? xm : fmaxf(xm, xs);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = !wild && fabsf(acc[i]) < INFINITY ? acc[i] : INFINITY;
+        } else {
+            xm = fmaxf(xm, xs);
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float v = valid ? acc[i] : -INFINITY;
@@ -339,16 +351,22 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
             v3[i] = fmaxf(v3[i], t2);
         }
     };
+    // this lane's certified lower bound of slot i's maximum; -inf where infinite
+    // scores or norms leave none (the difference is then no number)
+    auto lower = [&](int i, float xb) __attribute__((always_inline)) {
+        return fmaxf(v1[i] - band(i, v1[i], xb), -INFINITY);
+    };
     // T from the scores so far.  With e <= ecap, v + ep <= v + 2^-22 |v| + 1.01
     // ecap, below M if v < M - 2 ecap - 2^-21 |M| (either sign of v and M); T
-    // takes 3 ecap and 2^-20 |M|, which also covers its own roundings.
+    // takes 3 ecap and 2^-20 |M|, which also covers its own roundings, and is
+    // -inf (no screen) where M or the band is infinite.
     auto refresh = [&]() __attribute__((always_inline)) {
         xcap = rowmax16(fmaxf(xcap, xm));   // the 16 rows are the same in each lane group
         const float xb = norm_up(xcap);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float M = rowmax16(v1[i] - band(i, v1[i], xb));
-            T[i] = M - (3.0f * fmaf(qk[i], xb, (float)D_ROW * 0x1p-120f) + fabsf(M) * 0x1p-20f);
+            const float M = rowmax16(lower(i, xb));
+            T[i] = fmaxf(M - (3.0f * fmaf(qk[i], xb, (float)D_ROW * 0x1p-120f) + fabsf(M) * 0x1p-20f), -INFINITY);
         }
     };
 
@@ -427,8 +445,9 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const bool hv = h0 + 4 * g + i < a.H && N > pbeg;
-            const float M = rowmax16(v1[i] - band(i, v1[i], xb));
-            auto reaches = [&](float v) __attribute__((always_inline)) { return v + band(i, v, xb) >= M; };
+            const float M = rowmax16(lower(i, xb));
+            // (not provably below M: a band that is no number reaches it)
+            auto reaches = [&](float v) __attribute__((always_inline)) { return !(v + band(i, v, xb) < M); };
             list(i, hv && r1[i] >= 0 && reaches(v1[i]), 0);
             list(i, hv && r2[i] >= 0 && reaches(v2[i]), 1);
         }
