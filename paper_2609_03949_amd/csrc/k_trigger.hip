@@ -239,7 +239,15 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
     }
     // the screen: a score below T[i] cannot reach the maximum (refresh below);
     // xcap is the largest finite ||x||^2 of the rows T allows for, xm this lane's
-    float T[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    // (slots past the last head, whose zero scores would always reach it, and
+    // those of a query that is no number, which has no maximum, pass nothing)
+    bool live[4];
+    float T[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        live[i] = h0 + 4 * g + i < a.H && qk[i] == qk[i];
+        T[i] = live[i] ? -INFINITY : INFINITY;
+    }
     float xcap = 0.f, xm = 0.f;
     // band half-width of a score v of slot i, xb >= ||x|| of every row: e >= KE
     // ||q|| ||x|| (one rounding, inside qk's slack; the n 2^-120 term keeps e
@@ -366,7 +374,8 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float M = rowmax16(lower(i, xb));
-            T[i] = fmaxf(M - (3.0f * fmaf(qk[i], xb, (float)D_ROW * 0x1p-120f) + fabsf(M) * 0x1p-20f), -INFINITY);
+            const float t = fmaxf(M - (3.0f * fmaf(qk[i], xb, (float)D_ROW * 0x1p-120f) + fabsf(M) * 0x1p-20f), -INFINITY);
+            T[i] = live[i] ? t : INFINITY;
         }
     };
 
@@ -444,7 +453,7 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
         };
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const bool hv = h0 + 4 * g + i < a.H && N > pbeg;
+            const bool hv = live[i] && N > pbeg;
             const float M = rowmax16(lower(i, xb));
             // (not provably below M: a band that is no number reaches it)
             auto reaches = [&](float v) __attribute__((always_inline)) { return !(v + band(i, v, xb) < M); };
@@ -475,7 +484,7 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
         double bv = best[i];
 #pragma unroll
         for (int o = 1; o < 16; o <<= 1) bv = fmax(bv, __shfl_xor(bv, o));
-        const bool miss = h0 + 4 * g + i < a.H && v3[i] > -INFINITY && !((double)(v3[i] + band(i, v3[i], xb)) < bv);
+        const bool miss = live[i] && v3[i] > -INFINITY && !((double)(v3[i] + band(i, v3[i], xb)) < bv);
         classes |= ((__ballot(miss) >> (16 * g)) & 0xFFFFull) << (16 * i);
     }
 #pragma unroll 1
