@@ -376,6 +376,10 @@ int vkv_step_run(vkv_ctx* ctx, const vkv_step* st, void* ws, size_t ws_bytes, in
  *   rows    [B, nrows] int32 (each list in [0, A)), or NULL for the whole archive [0, A)
  *   add_recent != 0: the recent window [A, T) is part of the list
  *   smax    [B, H] fp64 (-inf for an empty list), argmax [B, H] int32 (-1 then)
+ * Both outputs are updated while the call runs (argmax then holds -2 at times)
+ * and hold the result when it has finished.  The call is fastest where they are
+ * naturally aligned and in the context device's own memory; other outputs take
+ * one workgroup per sequence and 128 heads.
  * bf16 MFMA screening with a certified band, fp64 for the rows that can hold
  * the maximum: bit for bit the fp64 definition.
  */

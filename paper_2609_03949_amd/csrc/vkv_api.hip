@@ -718,7 +718,7 @@ int vkv_step_run(vkv_ctx* ctx, const vkv_step* st, void* ws, size_t ws_bytes, in
 }
 
 static hipError_t run_row_max(const vkv_step* st, const int32_t* rows, int64_t nrows, int all_archive, int add_recent,
-                              double* smax, int32_t* argmax, hipStream_t s, char* ws = nullptr) {
+                              double* smax, int32_t* argmax, hipStream_t s, char* ws, bool merge) {
     RowMaxArgs a{};
     // row ranges in parallel, about one workgroup per CU in all (a workgroup
     // holds 8 head groups of 16), at least 64 rows each.  With a workspace the
@@ -726,7 +726,8 @@ static hipError_t run_row_max(const vkv_step* st, const int32_t* rows, int64_t n
     // they are merged into the outputs, where many ranges of a sequence wait for
     // each other: beyond 64 of them a range is at least 256 rows (one sequence of
     // 32768 rows and 128 heads: 66 us in 128 ranges, 78 in 256; a list of 1088
-    // rows in 8 sequences: 40 us in 17 ranges, 48 in 4).
+    // rows in 8 sequences: 40 us in 17 ranges, 48 in 4).  Outputs that cannot be
+    // merged into take one range a sequence.
     const int64_t N = (all_archive ? st->T - st->W : nrows) + (add_recent ? st->W : 0);
     const int64_t blocks = ((st->H + 127) / 128) * st->B;
     const int64_t want = std::max<int64_t>(1, (256 + blocks - 1) / std::max<int64_t>(blocks, 1));
@@ -735,9 +736,11 @@ static hipError_t run_row_max(const vkv_step* st, const int32_t* rows, int64_t n
         const WsLayout L = layout(st, 0, 0);
         a.part_v = reinterpret_cast<double*>(ws + L.rmx);
         a.part_u = reinterpret_cast<int32_t*>(ws + L.rmx + (size_t)(st->B * st->H * RM_MAX_SPLIT * 8));
-    } else {
+    } else if (merge) {
         const int64_t most = std::max<int64_t>({(int64_t)1, std::min<int64_t>(N / 64, 64), N / 256});
         a.nsplit = (int)std::min(want, most);
+    } else {
+        a.nsplit = 1;
     }
     a.q_lat = st->q_lat;
     a.q_rope = st->q_rope;
@@ -757,6 +760,18 @@ static hipError_t run_row_max(const vkv_step* st, const int32_t* rows, int64_t n
     return launch_row_max(a, s);
 }
 
+// May a kernel update p with atomics?  It must be naturally aligned, and in this
+// device's own memory: over the host link an atomic may do nothing (0.2 us a call).
+static bool takes_atomics(const vkv_ctx* ctx, const void* p, size_t align) {
+    hipPointerAttribute_t at{};
+    if ((uintptr_t)p % align) return false;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == ctx->device;
+}
+
 int vkv_row_max(vkv_ctx* ctx, const vkv_step* st, const int32_t* rows, int64_t nrows, int32_t add_recent,
                 double* smax, int32_t* argmax, void* stream) {
     if (!ctx) return fail(nullptr, VKV_E_ARG, "ctx is NULL");
@@ -765,7 +780,10 @@ int vkv_row_max(vkv_ctx* ctx, const vkv_step* st, const int32_t* rows, int64_t n
     if (!smax || !argmax) return fail(ctx, VKV_E_ARG, "smax and argmax are required");
     if (rows && (nrows < 0 || nrows > st->T - st->W))
         return fail(ctx, VKV_E_ARG, "nrows=%lld outside [0, A]", (long long)nrows);
-    HIP_TRY(ctx, run_row_max(st, rows, nrows, rows ? 0 : 1, add_recent ? 1 : 0, smax, argmax, (hipStream_t)stream));
+    // ranges merged in the outputs use device-wide atomics on them (k_trigger.hip)
+    const bool merge = takes_atomics(ctx, smax, 8) && takes_atomics(ctx, argmax, 4);
+    HIP_TRY(ctx, run_row_max(st, rows, nrows, rows ? 0 : 1, add_recent ? 1 : 0, smax, argmax, (hipStream_t)stream, nullptr,
+                             merge));
     return VKV_OK;
 }
 
@@ -893,7 +911,7 @@ int vkv_step_run_trigger(vkv_ctx* ctx, const vkv_step* st, void* ws, size_t ws_b
     HIP_TRY(ctx, run_score(st, w, all, key, ub, cert_mult, s));
     HIP_TRY(ctx, run_select(st, w, all, k, sel, theta, s));
     // the tier-1 maximum logit per head over S and the recent window
-    HIP_TRY(ctx, run_row_max(st, sel, k, 0, 1, smax, argmax, s, w));
+    HIP_TRY(ctx, run_row_max(st, sel, k, 0, 1, smax, argmax, s, w, false));
     HIP_TRY(ctx, run_trigger(st, w, k, sel, ub, cert_mult, smax, topj, fired, fired_count, cap, s));
     HIP_TRY(ctx, run_attend(st, w, all, k, sel, fired, fired_count, cap, scale, out, lse, s));
     if ((rc = debug_check_sel(ctx, st, k, sel, s))) return rc;
@@ -983,7 +1001,7 @@ int vkv_step_run_kept(vkv_ctx* ctx, const vkv_step* st, void* ws, size_t ws_byte
     // and the scan writes the trigger margins max_h (UB~_h - s*_h) directly
     HIP_TRY(ctx, run_prep(st, w, all, s));
     HIP_TRY(ctx, launch_mark_tier(reinterpret_cast<uint8_t*>(w + L.flags), flag_stride(L.A), L.A, (int)st->B, kept, k, s));
-    HIP_TRY(ctx, run_row_max(st, kept, k, 0, 1, smax, argmax, s, w));
+    HIP_TRY(ctx, run_row_max(st, kept, k, 0, 1, smax, argmax, s, w, false));
     // the step reads only the margins: without a key buffer the scan writes no keys
     HIP_TRY(ctx, run_score(st, w, all, key, ub, cert_mult, s, smax, key == nullptr));
     HIP_TRY(ctx, run_trigger(st, w, k, kept, ub, cert_mult, smax, topj, fired, fired_count, cap, s));

@@ -52,3 +52,31 @@ def test_row_max_over_ranges(B, H, T, W, copies):
                 assert np.array_equal(got_s[b], want[b][0])
                 assert np.array_equal(got_a[b], want[b][1])
     ctx.close()
+
+
+@pytest.mark.parametrize("where", ["device", "smax off 8", "argmax off 4", "pinned host"])
+def test_outputs_that_take_no_atomics(where):
+    """Outputs that are not naturally aligned, or lie in host memory, take one range
+    a sequence and plain stores; the result and the bytes around it are the same."""
+    B, H, T, W = 2, 24, 6000, 40
+    wl = synth.make_workload(synth.CONFIGS["cfg1"].with_(B=B, H=H, T=T, W=W, k=0, needles=3), "cuda", seed=11)
+    step = vkv.Step(wl["cache"], wl["q_lat"], wl["q_rope"], W, synth.MODE_ROPE)
+    n = B * H
+    so, ao = 8 + (4 if where == "smax off 8" else 0), 8 + (2 if where == "argmax off 4" else 0)
+    host = where == "pinned host"
+    raw = [torch.full((size,), 0x5A, dtype=torch.uint8, device="cpu" if host else "cuda") for size in (8 * n + 32, 4 * n + 32)]
+    if host:
+        raw = [t.pin_memory() for t in raw]
+    ctx = vkv.Context(0)
+    ctx.check(ctx.lib.vkv_row_max(ctx.handle, step.ref, None, 0, 1, raw[0].data_ptr() + so, raw[1].data_ptr() + ao, None))
+    torch.cuda.synchronize()
+    ctx.close()
+    s, a = (t.cpu().numpy() for t in raw)
+    assert (s[:so] == 0x5A).all() and (s[so + 8 * n:] == 0x5A).all()
+    assert (a[:ao] == 0x5A).all() and (a[ao + 4 * n:] == 0x5A).all()
+    gs = np.frombuffer(s[so:so + 8 * n].tobytes(), np.float64).reshape(B, H)
+    ga = np.frombuffer(a[ao:ao + 4 * n].tobytes(), np.int32).reshape(B, H)
+    bits, ql, qr = (synth.to_numpy_bits(wl[x]) for x in ("cache", "q_lat", "q_rope"))
+    for b in range(B):
+        ws, wa = oracle.row_max(ql[b], qr[b], bits[b], np.arange(T, dtype=np.int32))
+        assert np.array_equal(gs[b], ws) and np.array_equal(ga[b], wa)
