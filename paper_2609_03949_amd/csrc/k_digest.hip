@@ -53,6 +53,17 @@ static_assert(DG_LDS <= 160 * 1024, "the CU's LDS");
 // workgroup barrier for exchanges through LDS (global loads stay in flight)
 __device__ __forceinline__ void dg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// the certificate scalars of row o of [B][T] from ||c||^2, ||y||^2 and ||d - y||^2
+__device__ __forceinline__ void cert_scalars(const DigestArgs& a, int64_t o, double Nc, double Ny, double Ne) {
+    const double G = CERT_G;
+    const double Dm = G * (double)ru_sqrt_f32((double)a.r * Nc);
+    const double sy = (double)ru_sqrt_f32(Ny);
+    const double X = ((Nc - Ny) + G * (Nc + Ny)) + (2.0 * Dm) * sy;
+    a.eta[o] = ru_sqrt_f32((X > 0.0 ? X : 0.0) * (1.0 + G));
+    a.eps[o] = ru_f32((double)ru_sqrt_f32(Ne) * (1.0 + G) + Dm);
+    a.gam[o] = ru_f32(sy * (1.0 + G) + Dm);
+}
+
 __global__ __launch_bounds__(DG_THREADS, 2) void digest_kernel(DigestArgs a, int rows) {
     extern __shared__ __align__(16) uint8_t dg_lds[];
     double* s_hand = reinterpret_cast<double*>(dg_lds + 4 * DG_HALF);
@@ -70,7 +81,7 @@ __global__ __launch_bounds__(DG_THREADS, 2) void digest_kernel(DigestArgs a, int
     uint16_t* ib = a.index ? a.index + (int64_t)b * a.ibs + u0 * a.is : nullptr;
     const int off = a.with_rope ? D_ROPE : 0;
     const bool cert = a.eta != nullptr;
-    const int nchunk = a.r > 0 ? (a.r + DG_CHUNK - 1) / DG_CHUNK : 1;
+    const int nchunk = (a.r + DG_CHUNK - 1) / DG_CHUNK;   // (r > 0)
     uint8_t* s_t = dg_lds + half * 2 * DG_HALF;    // this half's two buffers
 
     // loader: wave jw of a half moves its dims of tile rows 4 jw .. 4 jw + 3, two
@@ -133,20 +144,12 @@ __global__ __launch_bounds__(DG_THREADS, 2) void digest_kernel(DigestArgs a, int
     auto scalars = [&](int grp) __attribute__((always_inline)) {
         const int rr = DG_GROUP * grp + tid;
         if (tid >= DG_GROUP || rr >= nrows) return;
-        const double Nc = s_nc[tid], Ny = s_acc[2 * tid], Ne = s_acc[2 * tid + 1];
-        const double G = CERT_G;
-        const double Dm = G * (double)ru_sqrt_f32((double)a.r * Nc);
-        const double sy = (double)ru_sqrt_f32(Ny);
-        const double X = ((Nc - Ny) + G * (Nc + Ny)) + (2.0 * Dm) * sy;
-        const int64_t o = (int64_t)b * a.T + u0 + rr;
-        a.eta[o] = ru_sqrt_f32((X > 0.0 ? X : 0.0) * (1.0 + G));
-        a.eps[o] = ru_f32((double)ru_sqrt_f32(Ne) * (1.0 + G) + Dm);
-        a.gam[o] = ru_f32(sy * (1.0 + G) + Dm);
+        cert_scalars(a, (int64_t)b * a.T + u0 + rr, s_nc[tid], s_acc[2 * tid], s_acc[2 * tid + 1]);
     };
 
     for (int ch = 0; ch < nchunk; ++ch) {
         const int j0 = ch * DG_CHUNK;
-        const int jn = a.r > 0 ? min(DG_CHUNK, a.r - j0) : 0;
+        const int jn = min(DG_CHUNK, a.r - j0);
         // (a wave without a basis tile multiplies zeros and contributes zeros)
         const bool active = 16 * jw < jn;
         const bool nc_on = cert && ch == 0 && half == 0;
@@ -279,8 +282,65 @@ __global__ __launch_bounds__(DG_THREADS, 2) void digest_kernel(DigestArgs a, int
     if (cert) scalars((ntile - 1) / DG_GTILES);
 }
 
+// An index without a digest (r = 0): the branch copy and, with the certificate,
+// eta >= ||c||.  One wave per 64 rows, without LDS, so that many share a CU: 8
+// lanes per row copy its branch, then each lane runs one row's sequential sum, a
+// cache line of the row (64 elements) in flight beside the one it adds.  Bound by
+// the row reads: 16 x 32768 rows 134 us with the certificate (4.5 TB/s), 22
+// without, 698 and 612 as a projection on no basis rows.
+__global__ __launch_bounds__(64) void digest_plain_kernel(DigestArgs a) {
+    const int b = blockIdx.y, lane = threadIdx.x;
+    const int64_t u0 = (int64_t)blockIdx.x * 64;
+    const int nrows = (int)min((int64_t)64, a.T - u0);
+    const uint16_t* cb = a.cache + (int64_t)b * a.cbs + u0 * a.cs;
+    if (a.index && a.with_rope) {
+        uint16_t* ib = a.index + (int64_t)b * a.ibs + u0 * a.is;
+        u16x8_t v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            v[e] = *reinterpret_cast<const u16x8_t*>(cb + (int64_t)min(8 * e + (lane >> 3), nrows - 1) * a.cs + D_LAT +
+                                                     8 * (lane & 7));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int rr = 8 * e + (lane >> 3);
+            if (rr < nrows) *reinterpret_cast<u16x8_t*>(ib + (int64_t)rr * a.is + 8 * (lane & 7)) = v[e];
+        }
+    }
+    if (!a.eta) return;
+    const uint16_t* row = cb + (int64_t)min(lane, nrows - 1) * a.cs;
+    u16x8_t x[2][8];
+    auto load = [&](int p, int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[buf][j] = *reinterpret_cast<const u16x8_t*>(row + 64 * p + 8 * j);
+    };
+    double nc = 0.0;
+    auto add = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const double v = bf16_bits_f64(x[buf][j][e]);
+                nc = fma(v, v, nc);
+            }
+    };
+    load(0, 0);
+#pragma unroll 1
+    for (int p = 0; p < D_LAT / 64; p += 2) {
+        load(p + 1, 1);
+        add(0);
+        if (p + 2 < D_LAT / 64) load(p + 2, 0);
+        add(1);
+    }
+    if (lane < nrows) cert_scalars(a, (int64_t)b * a.T + u0 + lane, nc, 0.0, 0.0);
+}
+
 hipError_t launch_digest(const DigestArgs& a, hipStream_t s) {
     if (a.T <= 0) return hipSuccess;
+    if (a.r == 0) {
+        if (!a.eta && !(a.index && a.with_rope)) return hipSuccess;
+        hipLaunchKernelGGL(digest_plain_kernel, dim3((unsigned)((a.T + 63) / 64), (unsigned)a.B), dim3(64), 0, s, a);
+        return hipGetLastError();
+    }
     // Rows per block: several groups keep the widened basis in registers for
     // longer (3 of 100 us per group), one group where it takes several chunks
     // (their sums of all rows would not fit the LDS) or where blocks would be
