@@ -151,10 +151,7 @@ __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(
         if (!sums) {
             const bool more = ch + 1 < nchunk;
             if (more) load_chunk(ch + 1);
-            if (tile) {
-                double none = 0.0;
-                acc = mfma_f64_rowdot512<false>(qa, reinterpret_cast<const uint16_t*>(s_p[ch & 1] + pb_off), qa, none);
-            }
+            if (tile) acc = mfma_f64_rowdot512(qa, reinterpret_cast<const uint16_t*>(s_p[ch & 1] + pb_off));
             if (more) store_chunk(ch + 1);
         } else if (ch == 0) {
             // Nq of head lane mod 16, i ascending (eight elements per LDS read)

@@ -309,16 +309,12 @@ size_t sketch_workspace_bytes(int r) {
     return (size_t)D_LAT * D_LAT * 8 + 2 * (size_t)D_LAT * r * 8 + 2 * (size_t)r * r * 8 + 256;
 }
 
-// M x N tiles of 16 x 16; K is 512 or a panel's width
+// M x N tiles of 16 x 16; K is 512, or a whole panel's columns where the product is subtracted
 template <bool SUB>
-static hipError_t gemm(Mat A, Mat B, int M, int N, int K, double* Out, int64_t ldo, hipStream_t s) {
-    const dim3 g((unsigned)(M / 16), (unsigned)(N / 16));
-    if (K == D_LAT)
-        hipLaunchKernelGGL((sk_gemm_kernel<D_LAT / 16, SUB>), g, dim3(256), 0, s, A, B, Out, ldo);
-    else if (K == SK_PANEL)
-        hipLaunchKernelGGL((sk_gemm_kernel<SK_PANEL / 16, SUB>), g, dim3(256), 0, s, A, B, Out, ldo);
-    else
-        hipLaunchKernelGGL((sk_gemm_kernel<SK_PANEL / 32, SUB>), g, dim3(256), 0, s, A, B, Out, ldo);
+static hipError_t gemm(Mat A, Mat B, int M, int N, double* Out, int64_t ldo, hipStream_t s) {
+    constexpr int NST = (SUB ? SK_PANEL : D_LAT) / 16;
+    hipLaunchKernelGGL((sk_gemm_kernel<NST, SUB>), dim3((unsigned)(M / 16), (unsigned)(N / 16)), dim3(256), 0, s, A, B, Out,
+                       ldo);
     return hipGetLastError();
 }
 
@@ -350,7 +346,7 @@ hipError_t launch_sketch(const uint16_t* q, int64_t m, int r, int iters, void* w
         for (int p = 0; p < r; p += SK_PANEL) {
             const int w = r - p < SK_PANEL ? r - p : SK_PANEL, rest = r - p - w;
             double* Yp = src + p;
-            if ((e2 = gemm<false>(Mat{Yp, 1, r}, Mat{Yp, r, 1}, w, w, D_LAT, G, w, s)) != hipSuccess) return e2;
+            if ((e2 = gemm<false>(Mat{Yp, 1, r}, Mat{Yp, r, 1}, w, w, G, w, s)) != hipSuccess) return e2;
             const double* dp = d0 ? d0 + p : nullptr;
             if (w == SK_PANEL)
                 hipLaunchKernelGGL(sk_orth_kernel<SK_PANEL>, dim3(D_LAT / 64), dim3(128), 0, s, G, Yp, dp, dst + p,
@@ -362,19 +358,19 @@ hipError_t launch_sketch(const uint16_t* q, int64_t m, int r, int iters, void* w
             if (rest == 0) break;
             // T = X_p^T Y_rest, Y_rest -= X_p T
             const double* Xp = dst + p;
-            if ((e2 = gemm<false>(Mat{Xp, 1, r}, Mat{Yp + w, r, 1}, w, rest, D_LAT, G, rest, s)) != hipSuccess) return e2;
-            if ((e2 = gemm<true>(Mat{Xp, r, 1}, Mat{G, rest, 1}, D_LAT, rest, w, Yp + w, r, s)) != hipSuccess) return e2;
+            if ((e2 = gemm<false>(Mat{Xp, 1, r}, Mat{Yp + w, r, 1}, w, rest, G, rest, s)) != hipSuccess) return e2;
+            if ((e2 = gemm<true>(Mat{Xp, r, 1}, Mat{G, rest, 1}, D_LAT, rest, Yp + w, r, s)) != hipSuccess) return e2;
         }
         return hipSuccess;
     };
     for (int t = 0; t <= iters; ++t) {
         // Y = C X (the start pattern on the first round), then X = orth(Y)
-        if ((e = gemm<false>(Mat{C, D_LAT, 1}, Mat{t == 0 ? nullptr : X, r, 1}, D_LAT, r, D_LAT, Y, r, s)) != hipSuccess)
+        if ((e = gemm<false>(Mat{C, D_LAT, 1}, Mat{t == 0 ? nullptr : X, r, 1}, D_LAT, r, Y, r, s)) != hipSuccess)
             return e;
         if ((e = orth(Y, X)) != hipSuccess) return e;
     }
     if ((e = orth(X, Y)) != hipSuccess) return e;   // the second pass: the basis is in Y
-    if (energy && (e = gemm<false>(Mat{C, D_LAT, 1}, Mat{Y, r, 1}, D_LAT, r, D_LAT, X, r, s)) != hipSuccess) return e;
+    if (energy && (e = gemm<false>(Mat{C, D_LAT, 1}, Mat{Y, r, 1}, D_LAT, r, X, r, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(basis_out_kernel, dim3((unsigned)r), dim3(256), 0, s, Y, energy ? X : nullptr, r, P, D0);
     if ((e = hipGetLastError()) != hipSuccess || !energy) return e;
     hipLaunchKernelGGL(energy_kernel, dim3(1), dim3(64), 0, s, D0, C, r, energy);
