@@ -282,6 +282,94 @@ __global__ __launch_bounds__(DG_THREADS, 2) void digest_kernel(DigestArgs a, int
     if (cert) scalars((ntile - 1) / DG_GTILES);
 }
 
+// Short sequences without a certificate (rows appended while decoding): the
+// widened basis of the kernel above costs a block 6 us before its first step,
+// which few rows do not repay.  Here a chunk of 64 basis rows is staged as bf16
+// and widened with the rows at each step; two streams of four waves (one 16-row
+// basis tile each) take alternate 16-row tiles through the whole 512-step chain,
+// each stream's next tile loading into registers beside it.  Rows and basis rows
+// sit in LDS rows padded to DS_ROW bytes, so the operand reads (16 rows, one
+// 16-bit element each) fall into distinct banks.
+constexpr int DS_ROW = 1040;
+constexpr int DS_MAX_T = 128;   // rows of a sequence up to which this form is used (launch_digest)
+
+__global__ __launch_bounds__(DG_THREADS) void digest_short_kernel(DigestArgs a, int rows) {
+    __shared__ __align__(16) uint8_t s_p[DG_CHUNK * DS_ROW];    // a chunk of basis rows
+    __shared__ __align__(16) uint8_t s_c[2][2][16 * DS_ROW];    // per stream, two tiles of cache rows
+    const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int st = wave >> 2, jw = wave & 3;   // row stream, basis tile of the chunk
+    const int64_t u0 = (int64_t)blockIdx.x * rows;
+    const int nrows = (int)min((int64_t)rows, a.T - u0);
+    const int ntile = (nrows + 15) / 16, niter = (ntile + 1) / 2;   // stream st takes tiles 2 it + st
+    const uint16_t* cb = a.cache + (int64_t)b * a.cbs + u0 * a.cs;
+    uint16_t* ib = a.index + (int64_t)b * a.ibs + u0 * a.is;
+    const int off = a.with_rope ? D_ROPE : 0;
+    // a tile's rows 4 jw .. 4 jw + 3, one 1 KB load each (rows past the end re-read
+    // the last one; nothing of them is stored)
+    u32x4_t nx[4];
+    auto load_tile = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            nx[q] = *reinterpret_cast<const u32x4_t*>(cb + (int64_t)min(16 * t + 4 * jw + q, nrows - 1) * a.cs + 8 * lane);
+    };
+    auto store_tile = [&](int it) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<u32x4_t*>(s_c[st][it & 1] + (4 * jw + q) * DS_ROW + 16 * lane) = nx[q];
+    };
+    load_tile(st);
+    if (a.with_rope) {   // the branch copy: up to 128 rows x 128 B
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int rr = 64 * e + (tid >> 3);
+            if (rr < nrows)
+                *reinterpret_cast<u16x8_t*>(ib + (int64_t)rr * a.is + 8 * (tid & 7)) =
+                    *reinterpret_cast<const u16x8_t*>(cb + (int64_t)rr * a.cs + D_LAT + 8 * (tid & 7));
+        }
+    }
+    for (int j0 = 0; j0 < a.r; j0 += DG_CHUNK) {
+        const int jn = min(DG_CHUNK, a.r - j0);
+        const bool active = 16 * jw < jn;
+        u32x4_t pr[DG_CHUNK / 8];
+#pragma unroll
+        for (int e = 0; e < DG_CHUNK / 8; ++e)
+            pr[e] = *reinterpret_cast<const u32x4_t*>(a.P + (int64_t)min(j0 + 8 * e + wave, a.r - 1) * D_LAT + 8 * lane);
+        if (j0 > 0) {
+            load_tile(st);
+            dg_barrier();   // the previous chunk's reads are done
+        }
+#pragma unroll
+        for (int e = 0; e < DG_CHUNK / 8; ++e)
+            *reinterpret_cast<u32x4_t*>(s_p + (8 * e + wave) * DS_ROW + 16 * lane) = pr[e];
+        store_tile(0);
+        dg_barrier();
+        // operand rows: A = cache row (lane mod 16) of the tile, B = basis row
+        // 16 jw + (lane mod 16) of the chunk; element k = lane / 16 of each step
+        const uint16_t* pb = reinterpret_cast<const uint16_t*>(s_p + (16 * jw + (lane & 15)) * DS_ROW) + (lane >> 4);
+        for (int it = 0; it < niter; ++it) {
+            const int t = 2 * it + st;
+            const bool more = it + 1 < niter;
+            if (more) load_tile(t + 2);
+            if (active && t < ntile) {
+                const uint16_t* ca =
+                    reinterpret_cast<const uint16_t*>(s_c[st][it & 1] + (lane & 15) * DS_ROW) + (lane >> 4);
+                const f64x4_t acc = mfma_f64_rowdot512(ca, pb);
+                // acc[i] = y of tile row 4 i + lane / 16, basis row j0 + 16 jw + lane mod 16
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int rr = 16 * t + 4 * i + (lane >> 4);
+                    if (rr < nrows)
+                        ib[(int64_t)rr * a.is + off + j0 + 16 * jw + (lane & 15)] = f64_to_bf16_rne(acc[i]);
+                }
+            }
+            if (more) {
+                store_tile(it + 1);
+                dg_barrier();   // (the stage it fills was last read before the barrier of it - 1)
+            }
+        }
+    }
+}
+
 // An index without a digest (r = 0): the branch copy and, with the certificate,
 // eta >= ||c||.  One wave per 64 rows, without LDS, so that many share a CU: 8
 // lanes per row copy its branch, then each lane runs one row's sequential sum, a
@@ -339,6 +427,17 @@ hipError_t launch_digest(const DigestArgs& a, hipStream_t s) {
     if (a.r == 0) {
         if (!a.eta && !(a.index && a.with_rope)) return hipSuccess;
         hipLaunchKernelGGL(digest_plain_kernel, dim3((unsigned)((a.T + 63) / 64), (unsigned)a.B), dim3(64), 0, s, a);
+        return hipGetLastError();
+    }
+    // Short sequences without a certificate, at r = 64 against the kernel below: one
+    // row 9 and 16 us, 64 rows 14 and 31, 1000 sequences of 17 rows 50 and 81, 300
+    // of 128 rows 97 and 104; at 300 of 256 rows the kernel below has caught up (a
+    // form of this one 200, that one 186).  32 rows a block, one tile per stream,
+    // as long as that starts no second round of blocks.
+    if (!a.eta && a.T <= DS_MAX_T) {
+        const int rows = a.B * ((a.T + 31) / 32) <= 256 ? 32 : DS_MAX_T;
+        hipLaunchKernelGGL(digest_short_kernel, dim3((unsigned)((a.T + rows - 1) / rows), (unsigned)a.B), dim3(DG_THREADS),
+                           0, s, a, rows);
         return hipGetLastError();
     }
     // Rows per block: several groups keep the widened basis in registers for

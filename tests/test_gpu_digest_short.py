@@ -1,5 +1,7 @@
 """The index builds that have a kernel of their own: no digest (r = 0: the branch
-copy and eta >= ||c||), around its 64-row blocks.  Bit for bit against the fp64
+copy and eta >= ||c||), around its 64-row blocks, and short sequences without a
+certificate (up to 128 rows), around its 16-row tiles, 32- and 128-row blocks and
+64-row basis chunks, against the long form just above.  Bit for bit against the fp64
 oracle, and nothing written past a row's columns or past the last row.
 """
 import numpy as np
@@ -54,3 +56,13 @@ def check(B, T, r, with_rope, cert, has_index=True, stride=576):
 def test_index_without_a_digest(B, T, with_rope, cert, has_index, stride):
     print(f"[digest-plain] B={B} T={T} rope={with_rope} cert={cert} index={has_index} stride={stride}", flush=True)
     check(B, T, 0, with_rope, cert, has_index, stride)
+
+
+@pytest.mark.parametrize("B,T,r,with_rope", [
+    (1, 1, 64, True), (1, 16, 32, False), (2, 17, 96, True), (3, 31, 512, True), (1, 32, 160, True), (5, 33, 64, True),
+    (64, 127, 64, True), (65, 128, 64, True), (300, 128, 32, False), (257, 17, 96, True), (260, 65, 160, True),
+    (2, 129, 96, True)])
+@pytest.mark.parametrize("stride", [576, 640])
+def test_short_index_without_a_certificate(B, T, r, with_rope, stride):
+    print(f"[digest-short] B={B} T={T} r={r} rope={with_rope} stride={stride}", flush=True)
+    check(B, T, r, with_rope, False, True, stride)
