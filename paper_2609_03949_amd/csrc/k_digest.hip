@@ -469,17 +469,26 @@ __device__ __forceinline__ double two_sum_add(double a, double b, int* inexact) 
     return s;
 }
 
-__global__ __launch_bounds__(256) void gram_rows_kernel(const uint16_t* P, int r, double* rowsum, double* flag) {
+// (Block j: row j.  It returns at once where every quick sum below is inside.)
+__global__ __launch_bounds__(256) void gram_rows_kernel(const uint16_t* P, int r, const double* fast, double* rowsum,
+                                                        double* flag) {
     __shared__ double s_g[512];
     __shared__ int s_f[512];
     const int j = blockIdx.x;
     const int tid = threadIdx.x;
+    bool inside = true;
+    for (int k = tid; k < r; k += 256) inside = inside && fast[k] <= GRAM_INSIDE;
+    if (__syncthreads_and(inside)) return;
     for (int k = tid; k < r; k += 256) {
+        const u16x8_t* pj = reinterpret_cast<const u16x8_t*>(P + (int64_t)j * D_LAT);
+        const u16x8_t* pk = reinterpret_cast<const u16x8_t*>(P + (int64_t)k * D_LAT);
         double gk = 0.0;
         int inexact = 0;
-        for (int i = 0; i < D_LAT; ++i) {
-            const double p = (double)bf16_to_f32(P[(int64_t)j * D_LAT + i]) * (double)bf16_to_f32(P[(int64_t)k * D_LAT + i]);
-            gk = two_sum_add(gk, p, &inexact);
+#pragma unroll 4
+        for (int p = 0; p < D_LAT / 8; ++p) {
+            const u16x8_t x = pj[p], y = pk[p];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) gk = two_sum_add(gk, bf16_bits_f64(x[e]) * bf16_bits_f64(y[e]), &inexact);
         }
         s_g[k] = gk;
         s_f[k] = inexact;
@@ -501,7 +510,9 @@ __global__ __launch_bounds__(256) void gram_rows_kernel(const uint16_t* P, int r
 // rows of P; four waves share a 16-column tile, a quarter of the dimensions
 // each, four tiles at a time; the sums in another order).  They decide the usual
 // case, a basis well inside the bound; only a row near the bound still needs the
-// sequential sums above.  38 -> 19 us at r = 64.
+// sequential sums above, formed behind them without a look at the host.  38 -> 19
+// us at r = 64, 2 of them the second launch; near the bound one row's build takes
+// 86 us as without the quick sums (118 where the host asked for the second launch).
 __global__ __launch_bounds__(1024) void gram_fast_kernel(const uint16_t* P, int r, double* rowsum) {
     __shared__ f64x4_t s_g[4][4][64];   // [column tile][quarter][lane]
     __shared__ double s_r[4][16];
@@ -543,14 +554,11 @@ __global__ __launch_bounds__(1024) void gram_fast_kernel(const uint16_t* P, int 
     if (tid < 16) rowsum[16 * blockIdx.x + tid] = (s_r[0][tid] + s_r[1][tid]) + (s_r[2][tid] + s_r[3][tid]);
 }
 
-hipError_t launch_gram_fast(const uint16_t* P, int r, double* rowsum, hipStream_t s) {
-    hipLaunchKernelGGL(gram_fast_kernel, dim3((unsigned)(r / 16)), dim3(1024), 0, s, P, r, rowsum);
-    return hipGetLastError();
-}
-
-hipError_t launch_gram_rows(const uint16_t* P, int r, double* rowsum, hipStream_t s) {
-    if (r <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gram_rows_kernel, dim3(r), dim3(256), 0, s, P, r, rowsum, rowsum + 512);
+hipError_t launch_gram(const uint16_t* P, int r, double* gram, hipStream_t s) {
+    hipLaunchKernelGGL(gram_fast_kernel, dim3((unsigned)(r / 16)), dim3(1024), 0, s, P, r, gram);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(gram_rows_kernel, dim3((unsigned)r), dim3(256), 0, s, P, r, gram, gram + r, gram + 2 * r);
     return hipGetLastError();
 }
 

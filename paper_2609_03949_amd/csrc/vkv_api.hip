@@ -11,6 +11,7 @@
 
 using namespace vkv;
 
+constexpr int GRAM_WORDS = 3 * D_LAT;
 constexpr int TIMING_SLOTS = 512;  // score launches timed between two vkv_score_timing calls
 
 // The workspace of vkv_step_run_static: one per device, held until the process
@@ -23,7 +24,7 @@ struct vkv_ctx {
     int device;
     int debug_rows;
     void* scratch_ptr;     // this device's address of `scratch`
-    double* gram;          // [1024] device scratch for the contractivity check
+    double* gram;          // [GRAM_WORDS] device scratch for the contractivity check
     int timing;            // vkv_step_run records events around its score launch
     hipEvent_t* tev;       // [2 * TIMING_SLOTS] start/end events of timed score launches
     int tcount;            // timed launches recorded since the last read
@@ -395,7 +396,7 @@ int vkv_create(vkv_ctx** out, int device) {
     }
     const char* dbg = getenv("VKV_DEBUG_ROWS");
     c->debug_rows = (dbg && dbg[0] && strcmp(dbg, "0") != 0) ? 1 : 0;
-    e = hipMalloc(&c->gram, 1024 * sizeof(double));
+    e = hipMalloc(&c->gram, GRAM_WORDS * sizeof(double));
     if (e != hipSuccess) {
         free(c);
         return fail(nullptr, VKV_E_HIP, "hipMalloc: %s", hipGetErrorString(e));
@@ -443,23 +444,18 @@ int vkv_digest_build(vkv_ctx* ctx, const uint16_t* cache, int64_t B, int64_t T, 
         // passes if its sum was computed exactly and is <= 1, or if it is <= 1 - 2^-30
         // (a margin far above the fp64 rounding of the sum).
         // Sums in any order differ from these by less than 2^-33 where a row passes
-        // (r times 512 products of sum at most 1, 2^-53 each, both ways), so rows
-        // of the quick sums below 1 - 2^-30 - 2^-33 pass; only where one does not
-        // are the sequential sums and their exactness flags formed.
-        std::vector<double> rows((size_t)1024);
-        HIP_TRY(ctx, launch_gram_fast(P, r, ctx->gram, s));
-        HIP_TRY(ctx, hipMemcpyAsync(rows.data(), ctx->gram, (size_t)r * 8, hipMemcpyDeviceToHost, s));
+        // (r times 512 products of sum at most 1, 2^-53 each, both ways), so quick
+        // sums of at most 1 - 2^-30 - 2^-33 pass; only where one is larger are the
+        // sequential sums and their exactness flags formed.
+        std::vector<double> rows((size_t)(3 * r));
+        HIP_TRY(ctx, launch_gram(P, r, ctx->gram, s));
+        HIP_TRY(ctx, hipMemcpyAsync(rows.data(), ctx->gram, (size_t)(3 * r) * 8, hipMemcpyDeviceToHost, s));
         HIP_TRY(ctx, hipStreamSynchronize(s));
         bool inside = true;
-        for (int j = 0; j < r; ++j) inside = inside && rows[(size_t)j] <= 1.0 - 0x1p-30 - 0x1p-33;
-        if (!inside) {
-            HIP_TRY(ctx, launch_gram_rows(P, r, ctx->gram, s));
-            HIP_TRY(ctx, hipMemcpyAsync(rows.data(), ctx->gram, 1024 * 8, hipMemcpyDeviceToHost, s));
-            HIP_TRY(ctx, hipStreamSynchronize(s));
-        }
+        for (int j = 0; j < r; ++j) inside = inside && rows[(size_t)j] <= GRAM_INSIDE;
         for (int j = 0; !inside && j < r; ++j) {
-            const double g = rows[(size_t)j];
-            const bool exact = rows[(size_t)(512 + j)] == 0.0;
+            const double g = rows[(size_t)(r + j)];
+            const bool exact = rows[(size_t)(2 * r + j)] == 0.0;
             if (!((exact && g <= 1.0) || g <= 1.0 - 0x1p-30))
                 return fail(ctx, VKV_E_NOT_CONTRACTIVE,
                             "Gershgorin bound of ||P||_2^2 is %.9g (row %d) > 1", g, j);

@@ -296,8 +296,11 @@ struct AttendArgs {
 hipError_t launch_qprep(const QprepArgs& a, hipStream_t s);
 hipError_t launch_score(const ScoreArgs& a, hipStream_t s);
 hipError_t launch_digest(const DigestArgs& a, hipStream_t s);
-hipError_t launch_gram_fast(const uint16_t* P, int r, double* rowsum, hipStream_t s);
-hipError_t launch_gram_rows(const uint16_t* P, int r, double* rowsum, hipStream_t s);
+// Gershgorin row sums of P P^T: quick sums in gram[0, r) and, unless all of them
+// are at most GRAM_INSIDE, the sequential ones in [r, 2 r) and their inexactness in
+// [2 r, 3 r)
+constexpr double GRAM_INSIDE = 1.0 - 0x1p-30 - 0x1p-33;
+hipError_t launch_gram(const uint16_t* P, int r, double* gram, hipStream_t s);
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 hipError_t launch_admit(const SelectArgs& a, hipStream_t s);
 hipError_t launch_attend(const AttendArgs& a, hipStream_t s);
