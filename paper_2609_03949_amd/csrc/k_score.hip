@@ -39,29 +39,31 @@ namespace vkv {
 // the step state of sequence b.
 // Bound by that latency: 6.5 us per chunk (128 dependent matrix steps and the
 // widening of their operands), and about 9 us of launch, first loads and the last
-// chunk's sums.  Chunks of 128 rows, staged before their chains and with their
-// sums after them, measured 18.9 / 30.0 / 32.1 us at r = 64 (32 x 128 heads), 160
-// (3 x 40) and 192 (4 x 128); this form 17.5 / 28.6 / 30.3.
+// chunk's sums.  Against chunks of 128 rows, staged before their chains and with
+// their sums after them, at 64 x 128 heads: 31.4 us at r = 64 (31.6), 57.4 at 160
+// (59.9), 131 at 512 (139).  At r = 96 a second chunk would leave half the SIMDs
+// idle: the six tiles go in one chunk, two SIMDs running two chains (64 x 40 heads
+// 19.3 us, 22.8 in two chunks).
 constexpr int QP_ROW = 1040;          // LDS bytes per staged row of 512 bf16
-constexpr int QP_CHUNK_ROWS = 64;     // basis rows staged at a time: one 16-row tile per wave
-constexpr int QP_MAX_WAVES = QP_CHUNK_ROWS / 16;
-constexpr int QP_WSTRIDE = QP_CHUNK_ROWS + 1;   // doubles per head of the staged w values (heads in distinct banks)
-constexpr int QP_DSTRIDE = QP_CHUNK_ROWS + 2;   // bf16 per head of their rounded values
-constexpr int QP_TAIL_BATCH = 16;              // staged values per LDS batch of the tail sums
+constexpr int QP_TAIL_BATCH = 16;     // staged values per LDS batch of the tail sums
 
 // waves with a basis tile (0 without a digest); one more wave takes the vector sums
+template <int ROWS>
 __host__ __device__ inline int qp_tile_waves(int r) {
     const int t = r / 16;
-    return t < 0 ? 0 : (t > QP_MAX_WAVES ? QP_MAX_WAVES : t);
+    return t > ROWS / 16 ? ROWS / 16 : t;
 }
 
 __device__ __forceinline__ void qp_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-__global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(QprepArgs a) {
-    __shared__ __align__(16) uint8_t s_q[16 * QP_ROW];                 // the block's 16 query rows, [h][i]
-    __shared__ __align__(16) uint8_t s_p[2][QP_CHUNK_ROWS * QP_ROW];   // two chunks of P rows
-    __shared__ double s_w[16 * QP_WSTRIDE];                            // a chunk's w values
-    __shared__ uint16_t s_d[16 * QP_DSTRIDE];                          // and RNE(w)
+// ROWS: basis rows staged at a time, one 16-row tile per wave; STAGES: 1 if r <= ROWS
+template <int ROWS, int STAGES>
+__global__ __launch_bounds__(64 * (ROWS / 16 + 1)) void qprep_project_kernel(QprepArgs a) {
+    constexpr int WS = ROWS + 1, DS = ROWS + 2;   // values per head of s_w and s_d (heads in distinct banks)
+    __shared__ __align__(16) uint8_t s_q[16 * QP_ROW];             // the block's 16 query rows, [h][i]
+    __shared__ __align__(16) uint8_t s_p[STAGES][ROWS * QP_ROW];   // chunks of P rows
+    __shared__ double s_w[16 * WS];                                // a chunk's w values
+    __shared__ uint16_t s_d[16 * DS];                              // and RNE(w)
     const int b = blockIdx.y, hb0 = 16 * blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -70,7 +72,7 @@ __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(
     }
     const int r = (a.mode & 2) ? a.r : 0;
     const int off = (a.mode & 1) ? D_ROPE : 0;
-    const int ntw = qp_tile_waves(r);
+    const int ntw = qp_tile_waves<ROWS>(r);
     const bool sums = wave == ntw;   // the wave of the vector sums
     // its lane 4 hl + t: rope pieces t and t + 4 of head hb0 + hl (loaded now, stored at the end)
     const int hl = lane >> 2, t = lane & 3;
@@ -88,14 +90,14 @@ __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(
     auto load_chunk = [&](int ch) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int row = min(QP_CHUNK_ROWS * ch + 16 * wave + e, r - 1);
+            const int row = min(ROWS * ch + 16 * wave + e, r - 1);
             nx[e] = *reinterpret_cast<const u32x4_t*>(a.P + (int64_t)row * D_LAT + 8 * lane);
         }
     };
     auto store_chunk = [&](int ch) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            *reinterpret_cast<u32x4_t*>(s_p[ch & 1] + (16 * wave + e) * QP_ROW + 16 * lane) = nx[e];
+            *reinterpret_cast<u32x4_t*>(s_p[ch % STAGES] + (16 * wave + e) * QP_ROW + 16 * lane) = nx[e];
     };
     if (!sums) {
         load_chunk(0);
@@ -120,8 +122,8 @@ __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(
     // t=1 ||w||^2, t=2 ||qd - w||^2, t=3 ||qd||^2 (t=0 takes Nq at the end)
     double tsum = 0.0;
     auto tail = [&](int nj) __attribute__((always_inline)) {
-        const double* w = s_w + hl * QP_WSTRIDE;
-        const uint16_t* dq = s_d + hl * QP_DSTRIDE;
+        const double* w = s_w + hl * WS;
+        const uint16_t* dq = s_d + hl * DS;
         // the three sums share one loop: x = w, qd - w or qd by lane (qd - 0
         // is qd exactly), chosen by selects.  The staged values are read in
         // batches, all reads of a batch in flight before its chain starts.
@@ -142,16 +144,16 @@ __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(
             }
         }
     };
-    const int nchunk = (r + QP_CHUNK_ROWS - 1) / QP_CHUNK_ROWS;
+    const int nchunk = (r + ROWS - 1) / ROWS;
     for (int ch = 0; ch < (nchunk > 0 ? nchunk : 1); ++ch) {
-        const int j0 = ch * QP_CHUNK_ROWS;
-        const int nj = min(QP_CHUNK_ROWS, r - j0);   // basis rows of this chunk (<= 0 without a digest)
+        const int j0 = ch * ROWS;
+        const int nj = min(ROWS, r - j0);   // basis rows of this chunk (<= 0 without a digest)
         const bool tile = !sums && 16 * wave < nj;
         f64x4_t acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
         if (!sums) {
             const bool more = ch + 1 < nchunk;
             if (more) load_chunk(ch + 1);
-            if (tile) acc = mfma_f64_rowdot512(qa, reinterpret_cast<const uint16_t*>(s_p[ch & 1] + pb_off));
+            if (tile) acc = mfma_f64_rowdot512(qa, reinterpret_cast<const uint16_t*>(s_p[ch % STAGES] + pb_off));
             if (more) store_chunk(ch + 1);
         } else if (ch == 0) {
             // Nq of head lane mod 16, i ascending (eight elements per LDS read)
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(
                 }
             }
         } else {
-            tail(QP_CHUNK_ROWS);   // of the chunk before
+            tail(ROWS);   // of the chunk before
         }
         qp_barrier();   // the tail's reads are done; s_w and s_d take this chunk's values
         if (tile) {
@@ -176,15 +178,15 @@ __global__ __launch_bounds__(64 * (QP_MAX_WAVES + 1)) void qprep_project_kernel(
                 const int hh = 4 * i + (lane >> 4), jl = 16 * wave + (lane & 15);
                 const double v = acc[i];
                 const uint16_t d = f64_to_bf16_rne(v);
-                s_w[hh * QP_WSTRIDE + jl] = v;
-                s_d[hh * QP_DSTRIDE + jl] = d;
+                s_w[hh * WS + jl] = v;
+                s_d[hh * DS + jl] = d;
                 if (hb0 + hh < a.H) a.qt[((int64_t)b * a.H + hb0 + hh) * a.n + off + j0 + jl] = d;
             }
         }
         qp_barrier();   // the next chunk's rows and this one's values are in place
     }
     if (!sums) return;
-    if (nchunk > 0) tail(r - (nchunk - 1) * QP_CHUNK_ROWS);
+    if (nchunk > 0) tail(r - (nchunk - 1) * ROWS);
     // certificate scalars of each head (fp32 upper bounds; Lemma (Index
     // certificate) plus the bf16 rounding of the stored sketch; fixed fp64
     // evaluation order, the same as the oracle's):
@@ -258,7 +260,10 @@ __device__ __forceinline__ void store_head_maxima(const ScoreArgs& a, int b, int
 hipError_t launch_qprep(const QprepArgs& a, hipStream_t s) {
     const int r = (a.mode & 2) ? a.r : 0;
     dim3 g1((a.H + 15) / 16, a.B);
-    hipLaunchKernelGGL(qprep_project_kernel, g1, dim3(64 * (qp_tile_waves(r) + 1)), 0, s, a);
+    if (r == 96)
+        hipLaunchKernelGGL((qprep_project_kernel<96, 1>), g1, dim3(64 * (qp_tile_waves<96>(r) + 1)), 0, s, a);
+    else
+        hipLaunchKernelGGL((qprep_project_kernel<64, 2>), g1, dim3(64 * (qp_tile_waves<64>(r) + 1)), 0, s, a);
     return hipGetLastError();
 }
 

@@ -138,7 +138,9 @@ def _wide_bf16(rng, shape, lo, hi):
 
 
 @pytest.mark.parametrize("mode,r", [(synth.MODE_ROPE_DIGEST, 64), (synth.MODE_ROPE_DIGEST, 160),
-                                    (synth.MODE_DIGEST, 512), (synth.MODE_ROPE, 0)])
+                                    (synth.MODE_DIGEST, 512), (synth.MODE_ROPE, 0),
+                                    (synth.MODE_DIGEST, 32), (synth.MODE_ROPE_DIGEST, 96), (synth.MODE_DIGEST, 96),
+                                    (synth.MODE_DIGEST, 128), (synth.MODE_DIGEST, 224)])
 def test_query_prep_bit_exact_under_rounding(ctx, mode, r):
     """qt and the head certificate scalars against the oracle, bit for bit, with
     queries and basis spread over 2^60: the projection and ||q||^2 are fp64
