@@ -948,9 +948,10 @@ __global__ __launch_bounds__(SEL_THREADS) void compact_kernel(CompactArgs a) {
 // [LO, HI] as in the resolve block, the undecided rows get their exact keys and
 // ranks as there, and S is written from 64-row masks in LDS.  Bound by latency:
 // one read of the keys, a few LDS passes and the exact keys' round trips.
-// Measured against the four launches: 8064 rows, 16 heads 18.8 against 30.4 us;
-// 32512 rows, 128 heads 32.7 against 34.4 (8 sequences) and 42.9 against 42.3
-// (16), where one block's passes over its keys have caught up; hence the line.
+// Measured against the four launches (us): 8184 rows, 16 heads 16.0 and 27.4;
+// 16000 rows 20.6 and 28.8 (64 sequences), 28.1 and 38.5 (256); mostly equal keys
+// there 92.5 and 96.1.  32512 rows, 128 heads 32.7 and 34.4 (8 sequences), 42.9 and
+// 42.3 (16): there one block's passes over its keys have caught up, hence the line.
 constexpr int SMALL_A = 16384;
 constexpr int SMALL_LDS = RES_LDS - SMALL_A / 8;   // dynamic LDS (the masks are static)
 constexpr int SMALL_BIN_MAX = 64;     // keys of the k-th key's bin that need no refinement
@@ -987,6 +988,8 @@ __global__ __launch_bounds__(RES_THREADS, 1) void sel_small_kernel(SelectArgs a)
         s_theta = f64_to_ord(-INFINITY);
     }
     // the bin of the k-th largest key~; [lo, hi] shrinks to it while it holds many
+    // and is wider than E (the undecided rows reach 2 E past it on either side in
+    // any case: narrower bins only cost their rounds where many keys are equal)
     float sc = 0.f;
     int db = 0;
     for (int round = 0; round < 4; ++round) {
@@ -1008,7 +1011,7 @@ __global__ __launch_bounds__(RES_THREADS, 1) void sel_small_kernel(SelectArgs a)
         if (d >= 0) s_bin = d;
         lds_barrier();
         db = s_bin < 0 ? 0 : s_bin;
-        const bool many = sc > 0.f && s_h[db] > (uint32_t)SMALL_BIN_MAX && round < 3;
+        const bool many = sc > 0.f && 1.0f > E * sc && s_h[db] > (uint32_t)SMALL_BIN_MAX && round < 3;
         lds_barrier();   // the histogram is read out
         if (!many) break;
         const float nlo = rd_f32(edge_lo_of(db, lo, sc)), nhi = ru_f32(edge_hi_of(db, lo, hi, sc));
