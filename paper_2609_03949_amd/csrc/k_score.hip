@@ -760,7 +760,9 @@ __global__ __launch_bounds__(256, KS >= 10 ? 1 : 2) void score_stream_kernel(Sco
         float m = rvmax;
 #pragma unroll
         for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, shfl_xor_local(m, o));
-        const float v = coef * m;   // lane 16 g + c; for g = 3: max |s*_h| x 1, or 0
+        // lane 16 g + c; for g = 3: max |s*_h| x 1, or 0 (a term without a coefficient
+        // adds nothing, also where a row's scalar is infinite)
+        const float v = coef > 0.f ? coef * m : 0.f;
         to.bmm = ((shfl_local(v, 0) + shfl_local(v, 16)) + shfl_local(v, 32)) + shfl_local(v, 48);
     }
     score_finish(a, b, lane, to, UB);

@@ -82,3 +82,44 @@ def test_margins_without_keys(H, r):
         got.append((ub, fired, cnt, out, lse))
     ctx.close()
     assert all(torch.equal(x, y) for x, y in zip(*got)) and int(got[0][2].sum()) > 0
+
+
+@pytest.mark.parametrize("H,r,T", [(16, 64, 3000), (128, 64, 3000), (70, 160, 4000), (128, 192, 5000), (40, 512, 3000)])
+def test_masked_rows_leave_the_admission_of_the_others(H, r, T):
+    """Rows filled with the type's lowest value have an infinite certificate scalar;
+    the bound's error term is then infinite, no more, and every row's exact bound
+    decides: the other rows' selection and admission are the oracle's."""
+    print(f"[score-wide] masked rows H={H} r={r} T={T}", flush=True)
+    ctx = vkv.Context(0)
+    B, W, k = 2, 8, 100
+    cfg = synth.CONFIGS["cfg4"].with_(B=B, H=H, T=T, W=W, k=1, r=r, mode=3, needles=5, basis="orthonormal")
+    wl = synth.make_workload(cfg, "cuda", seed=T + r)
+    masked = np.arange(3, T, 97)
+    wl["cache"][:, torch.from_numpy(masked).cuda()] = float(torch.finfo(torch.bfloat16).min)
+    index = torch.empty(B, T, 64 + r, dtype=torch.bfloat16, device="cuda")
+    sc = [torch.empty(B, T, device="cuda") for _ in range(3)]
+    vkv.digest_build(ctx, wl["cache"], wl["P"], r, True, index, *sc)
+    step = vkv.Step(wl["cache"], wl["q_lat"], wl["q_rope"], W, 3, r, index=index, P=wl["P"], eta=sc[0], eps=sc[1], gam=sc[2])
+    A, cm = step.A, 0.2
+    ws = vkv.alloc_workspace(step, k)
+    sel = torch.empty(B, k, dtype=torch.int32, device="cuda")
+    theta = torch.empty(B, dtype=torch.float64, device="cuda")
+    ub, adm = torch.empty(B, A, device="cuda"), torch.full((B, A), -1, dtype=torch.int32, device="cuda")
+    cnt = torch.empty(B, dtype=torch.int32, device="cuda")
+    vkv.query_prep(ctx, step, ws)
+    vkv.score(ctx, step, ws, None, ub, cert_mult=cm)
+    vkv.select(ctx, step, ws, k, sel, theta)
+    vkv.admit(ctx, step, ws, k, sel, theta, ub, adm, cnt, A, cert_mult=cm)
+    torch.cuda.synchronize()
+    ctx.close()
+    bits = [synth.to_numpy_bits(wl[n]) for n in ("cache", "q_lat", "q_rope", "P")]
+    # the oracle on the same keys: the masked rows' own keys are what they are
+    qt, a, nq, e = oracle.query_prep(bits[1], bits[2], bits[3], r, 3)
+    for b in range(B):
+        x = oracle.index_rows(bits[0][b], synth.to_numpy_bits(index[b]), 3, r, True)
+        s = [v[b].cpu().numpy() for v in sc]
+        th = float(theta[b])
+        UB = oracle.upper_bounds(qt[b], a[b], nq[b], e[b], x, *s, A, cert_mult=cm)
+        want = np.setdiff1d(np.flatnonzero(UB > th), np.concatenate([sel[b].cpu().numpy(), masked]))
+        got = np.setdiff1d(adm[b, :int(cnt[b])].cpu().numpy(), masked)
+        assert len(want) > 0 and np.array_equal(got, want)
