@@ -273,11 +273,12 @@ def test_two_tier_capacity_overflow(ctx):
 
 # ------------------------------------------------------------ edge cases
 
-@pytest.mark.parametrize("H", [1, 8, 24, 64, 128])
-def test_head_counts(ctx, H):
-    say(f"heads H={H}")
+@pytest.mark.parametrize("H,T", [(1, 3000), (8, 3000), (24, 3000), (64, 3000), (128, 3000), (5, 20000), (24, 20000),
+                                 (100, 20000)])
+def test_head_counts(ctx, H, T):
+    say(f"heads H={H} T={T}")
     cfg = synth.CONFIGS["cfg4"].with_(H=H)
-    wl = synth.make_workload(cfg, "cuda", B=2, T=3000)
+    wl = synth.make_workload(cfg, "cuda", B=2, T=T)
     g, _ = gpu_step(ctx, wl, k=97)
     o, _ = oracle_step(wl, [0, 1], k=97)
     check_step(wl, g, o, [0, 1])
@@ -295,11 +296,15 @@ def test_widths(ctx, mode, r):
     check_step(wl, g, o, [0, 1])
 
 
+# Archives of up to 16384 rows are selected in one launch, longer ones in four: the
+# tests of ties, duplicates, budgets and heads run in both.
+
+@pytest.mark.parametrize("T", [2100, 18000])
 @pytest.mark.parametrize("k", [0, 1, 2, "A-1", "A"])
-def test_budget_extremes(ctx, k):
-    say(f"budget k={k}")
+def test_budget_extremes(ctx, k, T):
+    say(f"budget k={k} T={T}")
     cfg = synth.CONFIGS["cfg0"].with_(H=16)
-    wl = synth.make_workload(cfg, "cuda", T=2100)
+    wl = synth.make_workload(cfg, "cuda", T=T)
     kk = {"A-1": wl["A"] - 1, "A": wl["A"]}.get(k, k)
     g, _ = gpu_step(ctx, wl, k=kk)
     o, _ = oracle_step(wl, [0], k=kk)
@@ -349,11 +354,12 @@ def test_no_archive(ctx):
     check_step(wl, g, o, [0, 1])
 
 
-def test_all_equal_keys_take_lowest_indices(ctx):
+@pytest.mark.parametrize("T", [3000, 20000])
+def test_all_equal_keys_take_lowest_indices(ctx, T):
     """q_rope = 0 and a zero digest query: every key ties at 0."""
-    say("all ties")
+    say(f"all ties T={T}")
     cfg = synth.CONFIGS["cfg1"].with_(H=8)
-    wl = synth.make_workload(cfg, "cuda", B=2, T=3000)
+    wl = synth.make_workload(cfg, "cuda", B=2, T=T)
     wl["q_rope"].zero_()
     g, _ = gpu_step(ctx, wl, k=300)
     for b in range(2):
@@ -363,15 +369,16 @@ def test_all_equal_keys_take_lowest_indices(ctx):
     check_step(wl, g, o, [0, 1])
 
 
-def test_duplicated_rows_and_near_ties(ctx):
+@pytest.mark.parametrize("T,copies", [(4000, 3000), (20000, 15000)])
+def test_duplicated_rows_and_near_ties(ctx, T, copies):
     """Rows duplicated many times (exact ties of the exact key) and rows a
     few ulps apart at the threshold."""
-    say("duplicates / near ties")
+    say(f"duplicates / near ties T={T}")
     cfg = synth.CONFIGS["cfg4"].with_(H=16)
-    wl = synth.make_workload(cfg, "cuda", B=2, T=4000)
+    wl = synth.make_workload(cfg, "cuda", B=2, T=T)
     c = wl["cache"]
-    src = torch.randint(0, 50, (3000,), generator=torch.Generator().manual_seed(3)).cuda()
-    c[:, :3000] = c[:, src]
+    src = torch.randint(0, 50, (copies,), generator=torch.Generator().manual_seed(3)).cuda()
+    c[:, :copies] = c[:, src]
     # perturb some copies by one bf16 ulp in one coordinate
     bits = c.view(torch.int16)
     bits[:, 1000:1200, 5] += 1
@@ -380,45 +387,43 @@ def test_duplicated_rows_and_near_ties(ctx):
     check_step(wl, g, o, [0, 1])
 
 
-def test_bracket_missed_by_the_sample(ctx):
-    """The largest keys sit only at rows the strided key sample never reads
-    (A = 16384: the sample takes every 4th row); the counting pass finds the
-    sampled bracket wrong and redoes the histogram over the whole key range."""
-    say("sample miss")
+@pytest.mark.parametrize("A", [20480, 65536])
+def test_bracket_missed_by_the_sample(ctx, A):
+    """More than k of the largest keys sit only at rows the key sample never reads
+    (64 runs of 32 rows, (A - 32) / 63 apart): the bracket placed from the sample
+    lies below all of them, the counting pass finds at least k keys above it, and
+    the resolve block must redo the histogram over the whole key range."""
+    say(f"sample miss A={A}")
     cfg = synth.CONFIGS["cfg1"].with_(H=16, needles=0)
-    wl = synth.make_workload(cfg, "cuda", B=1, T=16384 + 256)
-    rows = torch.arange(1, 4096, 4, device="cuda")
-    wl["cache"][0, rows, 512:] = (wl["cache"][0, rows, 512:].float() * 8).to(torch.bfloat16)
-    g, _ = gpu_step(ctx, wl, k=256)
-    o, _ = oracle_step(wl, [0], k=256)
+    wl = synth.make_workload(cfg, "cuda", B=1, T=A + cfg.W)
+    assert wl["A"] == A
+    stride = (A - 32) // 63
+    u = np.arange(A)
+    # (u % stride < 32 are the sampled rows)
+    rows = u[(u % stride >= 40) & (u < 4 * stride)]
+    k = 2 * len(rows) // 3
+    at = torch.from_numpy(rows).cuda()
+    wl["cache"][0, at, 512:] = (wl["cache"][0, at, 512:].float() * 64).to(torch.bfloat16)
+    g, _ = gpu_step(ctx, wl, k=k)
+    o, _ = oracle_step(wl, [0], k=k)
+    sampled = np.concatenate([np.arange(32) + i * stride for i in range(64)])
+    # enough sampled keys above the threshold's place for the bracket to have an upper end
+    ks = k * 2048 / A
+    assert ks - 4 * np.sqrt(ks) - 16 >= 1
+    assert np.count_nonzero(o[0]["key"] > o[0]["key"][sampled].max() * (1 + 1e-5)) >= k
     check_step(wl, g, o, [0])
     assert set(g["sel"][0].tolist()) <= set(rows.tolist())
 
 
-def test_bracket_missed_by_the_sample_long_archive(ctx):
-    """The same miss on an archive of 65536 rows: the sample takes runs of 32
-    rows about 1040 apart, so rows 40..940 are never sampled; the largest keys
-    are planted there, and the bracket pass must fall back to the whole key
-    range of 32 counting blocks' worth of keys."""
-    say("sample miss, long archive")
-    cfg = synth.CONFIGS["cfg1"].with_(H=16, needles=0)
-    wl = synth.make_workload(cfg, "cuda", B=1, T=65536 + 256)
-    rows = torch.arange(40, 940, 3, device="cuda")
-    wl["cache"][0, rows, 512:] = (wl["cache"][0, rows, 512:].float() * 8).to(torch.bfloat16)
-    g, _ = gpu_step(ctx, wl, k=256)
-    o, _ = oracle_step(wl, [0], k=256)
-    check_step(wl, g, o, [0])
-    assert set(g["sel"][0].tolist()) <= set(rows.tolist())
-
-
-@pytest.mark.parametrize("H", [16, 128])
-def test_identical_heads_make_every_head_a_candidate(ctx, H):
+@pytest.mark.parametrize("T", [6000, 20000])
+@pytest.mark.parametrize("H", [16, 100, 128])
+def test_identical_heads_make_every_head_a_candidate(ctx, H, T):
     """All heads carry the same query: every head ties for the maximum of every
     ambiguous row, so all of them go through the fp64 pass (H = 16: as queued
     (row, head) pairs; H = 128: in the re-screening wave itself)."""
-    say(f"identical heads H={H}")
+    say(f"identical heads H={H} T={T}")
     cfg = synth.CONFIGS["cfg4"].with_(H=H)
-    wl = synth.make_workload(cfg, "cuda", B=1, T=6000)
+    wl = synth.make_workload(cfg, "cuda", B=1, T=T)
     wl["q_lat"][0] = wl["q_lat"][0, :1].expand(H, -1)
     wl["q_rope"][0] = wl["q_rope"][0, :1].expand(H, -1)
     g, _ = gpu_step(ctx, wl, k=500)
