@@ -35,18 +35,20 @@ def test_lowpass_residual(kappa, B, nblk, stride):
     assert np.max(np.abs(sigma.cpu().numpy() - want)) <= 1e-12 * np.linalg.norm(x[0, 0])
 
 
-def keys(kind, n, rng):
+def keys(kind, n, lo, rng):
     if kind == "chi":
         return np.sqrt(rng.chisquare(64, n))
     if kind == "ties":
         return np.round(rng.exponential(2.0, n) * 4) / 4
     if kind == "equal":
         return np.full(n, 3.25)
-    if kind == "sparse":      # the large keys sit between the sampled places
+    if kind == "sparse":      # the large keys sit between the sampled places (2048 at even spacing past the sinks)
         v = rng.random(n)
-        at = rng.choice(n, n // 20, replace=False)
+        at = rng.choice(n, n // 10, replace=False)
         v[at] += 100.0
-        v[::max(1, n // 2048)] = rng.random(len(v[::max(1, n // 2048)]))
+        sampled = lo + max(1, (n - lo) // 2048) * np.arange(2048)
+        sampled = sampled[sampled < n]
+        v[sampled] = rng.random(len(sampled))
         return v
     if kind == "wide":        # many octaves, zeros and infinities
         v = np.exp(rng.uniform(-600, 600, n))
@@ -63,7 +65,10 @@ def keys(kind, n, rng):
 def test_tier_is_the_stable_order(kind, n, m, nsink):
     rng = np.random.default_rng(n + m)
     B = 2
-    v = np.stack([keys(kind, n, rng) for _ in range(B)])
+    lo = min(nsink, n)
+    v = np.stack([keys(kind, n, lo, rng) for _ in range(B)])
+    if kind == "sparse" and (n, m) == (131072, 4092):
+        assert np.count_nonzero(v[0] >= 100.0) > m   # the bracket, placed from the sample, lies below them all
     sigma = torch.from_numpy(v).cuda()
     K = vkv.sigma_tier_size(n, m, nsink)
     kept = torch.full((B, K), -7, dtype=torch.int32, device="cuda")
@@ -71,7 +76,6 @@ def test_tier_is_the_stable_order(kind, n, m, nsink):
     vkv.sigma_select(ctx, sigma, n, m, nsink, kept)
     got = kept.cpu().numpy()
     ctx.close()
-    lo = min(nsink, n)
     for b in range(B):
         order = np.argsort(-v[b, lo:], kind="stable")[:K - lo] + lo
         want = np.concatenate([np.arange(lo), np.sort(order)])
