@@ -16,8 +16,8 @@
 // outputs where the caller gives no scratch.
 // Bound by the gathered row stream (1152-byte rows, 3.6 TB/s measured over a
 // whole archive) and, in short ranges, by the fp64 chains at the end (about
-// 12 us).  Measured: 16 x 32768 rows, 128 heads 2650 -> 164 us (one range per
-// sequence before), 32 x 4608 rows 97 -> 75 us and 16 x 1280 rows 41 -> 34 us
+// 12 us).  Measured: 16 x 32768 rows, 128 heads 2650 -> 169 us (one range per
+// sequence before), 32 x 4608 rows 97 -> 71 us and 16 x 1280 rows 41 -> 35 us
 // (candidate lists in LDS with a band and three cross-lane steps per score
 // before).
 //
@@ -218,12 +218,17 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
     // qk[i] = KE ||q|| inflated by 2^-19 (which covers the fp32 roundings of
     // qk and of the product with ||x|| below), KE = 2 (n + n/32) 2^-23
     constexpr float KE = 2.0f * (float)(D_ROW + D_ROW / 32) * 0x1p-23f;
-    float qk[4];
+    float qk[4], qmax = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const float qub = sqrtf(__shfl(qs, 4 * g + i) * (1.0f + 0x1p-12f)) * (1.0f + 0x1p-20f);
         qk[i] = (KE * qub) * (1.0f + 0x1p-19f);
+        qmax = fmaxf(qmax, qub);
     }
+    // ||x||^2 up to which this lane's scores, and the partial sums on the way, stay
+    // below 2^127: |sum| <= ||q|| ||x|| (0 for an infinite query)
+    const float q126 = 0x1p126f / qmax;
+    const float xlim = fminf(q126 * q126, 0x1.fffffep127f);
     // Per lane (tile-row class c) and head slot i: the three largest scores of
     // the rows it has seen and the rows of the first two.  The exact maximum of
     // a head is among the entries whose upper bound reaches its certified lower
@@ -238,7 +243,8 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
         r1[i] = r2[i] = -1;
     }
     // the screen: a score below T[i] cannot reach the maximum (refresh below);
-    // xcap is the largest finite ||x||^2 of the rows T allows for, xm this lane's
+    // xcap is the largest finite ||x||^2 of the rows T allows for (xskip, also at
+    // most xlim: rows up to it may be skipped), xm this lane's
     // (slots past the last head, whose zero scores would always reach it, and
     // those of a query that is no number, which has no maximum, pass nothing)
     bool live[4];
@@ -248,7 +254,7 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
         live[i] = h0 + 4 * g + i < a.H && qk[i] == qk[i];
         T[i] = live[i] ? -INFINITY : INFINITY;
     }
-    float xcap = 0.f, xm = 0.f;
+    float xcap = 0.f, xskip = 0.f, xm = 0.f;
     // band half-width of a score v of slot i, xb >= ||x|| of every row: e >= KE
     // ||q|| ||x|| (one rounding, inside qk's slack; the n 2^-120 term keeps e
     // away from the subnormals).  The rounding to nearest of v -+ ep moves it by
@@ -328,14 +334,12 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
         const float xs = s_xn[st][rl];
         // In a long range most halves hold no row that can reach any head's
         // bound: a comparison per score and one ballot skip the rest
-        const float all4 = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-        const bool odd = !(fabsf(all4) + xs < INFINITY);
-        bool maybe = odd || xs > xcap;
+        bool maybe = !(xs <= xskip);
 #pragma unroll
         for (int i = 0; i < 4; ++i) maybe |= acc[i] >= T[i];
         if (__ballot(maybe) == 0) return;
         const int32_t u = s_id[sid][rl];
-        if (__ballot(odd) != 0) {
+        if (__ballot(!(xs <= xlim)) != 0) {
             // A score that is not finite says nothing, and a row whose ||x||^2 is
             // past fp32 has no band: they rank first, so that their exact score
             // decides, and such a row does not widen the bands of the others
@@ -370,6 +374,7 @@ __global__ __launch_bounds__(RM_THREADS) void row_max_kernel(RowMaxArgs a) {
     // -inf (no screen) where M or the band is infinite.
     auto refresh = [&]() __attribute__((always_inline)) {
         xcap = rowmax16(fmaxf(xcap, xm));   // the 16 rows are the same in each lane group
+        xskip = fminf(xcap, xlim);
         const float xb = norm_up(xcap);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
