@@ -756,14 +756,16 @@ static hipError_t run_row_max(const vkv_step* st, const int32_t* rows, int64_t n
     return launch_row_max(a, s);
 }
 
-// May a kernel update p with atomics?  It must be naturally aligned, and in this
-// device's own memory: over the host link an atomic may do nothing (0.2 us a call).
+// May a kernel update p with atomics?  It must be naturally aligned, and not in
+// host or another device's memory: over a link an atomic may do nothing (0.2 us a
+// call).  Memory the runtime keeps no record of is the caller's own mapping of
+// device memory, as every pointer that a kernel may write is.
 static bool takes_atomics(const vkv_ctx* ctx, const void* p, size_t align) {
     hipPointerAttribute_t at{};
     if ((uintptr_t)p % align) return false;
     if (hipPointerGetAttributes(&at, p) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return true;
     }
     return at.type == hipMemoryTypeDevice && at.device == ctx->device;
 }

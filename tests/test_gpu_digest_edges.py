@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
     (1, 1, 64, True, True), (2, 15, 32, True, True), (1, 16, 64, False, False), (1, 17, 96, True, True),
     (3, 255, 160, True, True), (1, 257, 64, True, True), (2, 272, 512, False, True), (1, 1041, 0, True, True),
     (520, 257, 64, True, True), (700, 529, 32, True, False), (1100, 513, 64, True, True),
+    (1, 1041, 512, True, False), (2, 272, 96, False, False), (520, 300, 64, True, False),
 ])
 def test_index_build_edges(B, T, r, with_rope, cert):
     print(f"[digest-edges] B={B} T={T} r={r} rope={with_rope} cert={cert}", flush=True)
